@@ -208,13 +208,14 @@ __device__ void solve_cost_pair(const CostArgs& A, int64_t p, const Lds16& L, Sh
             }
         }
         __syncthreads();
-        round_buckets<T>(L, sh, mact, nact);
+        constexpr bool pack = sizeof(TD) == 4;  // FP32 entries leave room for the index
+        round_buckets_pos<T, CSMAX>(L, sh, mact, nact, pack);
         // keys are the distances themselves (metric code SQEUCLIDEAN: D = key)
-        round_rank<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, NNSEMD_SQEUCLIDEAN,
-                             A.protocol == NNSEMD_GREEDY ? &sh.tie_order : nullptr);
-        round_walk<T, true, true>(L, mact, NNSEMD_SQEUCLIDEAN, cost);
-        round_compact<T, CSMAX, 0, true>(L, sh, mact, nact, nnz, want_plan ? A.plan_src : nullptr, A.plan_dst,
-                                   A.plan_flow, plan_base);
+        round_rank_pos<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, pack);
+        round_walk_pos<T>(L, mact);
+        round_compact_pos<T, CSMAX, 0, true>(L, sh, mact, nact, nnz, want_plan ? A.plan_src : nullptr, A.plan_dst,
+                                             A.plan_flow, plan_base, NNSEMD_SQEUCLIDEAN,
+                                             A.protocol == NNSEMD_GREEDY, cost);
         ++rounds;
     }
 

@@ -1277,25 +1277,15 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
         work += (int64_t)mact * nact;
         near += ps::search_round<D, T, kLpTailChunk, L1>(L, sh, A.X, Yt, centre, rhat, mact, nact, 1, false,
                                                           A.metric);
-        rc::round_buckets<T>(L, sh, mact, nact);
-        rc::round_rank<T, kLpTailChunk>(L, nact, A.protocol, A.seed, (int)rounds, A.metric,
-                                        A.protocol == NNSEMD_GREEDY ? &sh.tie_order : nullptr);
+        rc::round_buckets_pos<T, kLpTailChunk>(L, sh, mact, nact, false);
+        rc::round_rank_pos<T, kLpTailChunk>(L, nact, A.protocol, A.seed, (int)rounds, false);
         // serve walk (the grid-wide rounds' operations and accumulators)
         for (int s = tid; s < mact; s += T) {
-            const int c = L.scnt[s];
-            if (c == 0) continue;
-            const int end = L.soff[s];
+            if (L.scnt[s] == 0) continue;
             const int isup = L.sidx[s];
-            int pos = end - c;
-            double sm = L.smass[s];
             double acc = A.w.costacc[isup];
-            while (pos < end && sm > 0.0) {
-                const int q = L.sorted[pos];
-                const double cm = L.cmass[q];
-                const double f = sm < cm ? sm : cm;
-                sm = sm - f;
-                L.cmass[q] = cm - f;
-                const double key = L.ckey[q];
+            rc::walk_supplier<T>(L, s, [&](int pos, int q, double f) {
+                const double key = L.ckey[pos];
                 acc = acc + f * (A.metric == NNSEMD_L2 ? sqrt(key) : key);
                 if (A.w.wsum != nullptr) {
                     A.w.wsum[isup] = A.w.wsum[isup] + f;
@@ -1304,16 +1294,14 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
                         A.w.bsum[(int64_t)isup * D + t] =
                             A.w.bsum[(int64_t)isup * D + t] + f * (double)Yt[(size_t)q * D + t];
                 }
-                L.ckey[q] = -f;  // negated flow: unserved claimants keep their keys
-                L.cnn[q] = isup;
-                ++pos;
-            }
-            L.smass[s] = sm;
+            });
             A.w.costacc[isup] = acc;
         }
         __syncthreads();
-        rc::round_compact<T, kLpTailChunk, RS, true>(L, sh, mact, nact, nnz, A.plan_src, A.plan_dst, A.plan_flow,
-                                               plan_base);
+        double unused = 0.0;
+        rc::round_compact_pos<T, kLpTailChunk, RS, false>(L, sh, mact, nact, nnz, A.plan_src, A.plan_dst,
+                                                          A.plan_flow, plan_base, A.metric,
+                                                          A.protocol == NNSEMD_GREEDY, unused);
         ++rounds;
     }
     // hand the state back to the finish: survivors in slots 0.. of the
@@ -1323,7 +1311,7 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
         A.w.smass[par][s] = L.smass[s];
     }
     for (int q = tid; q < nact; q += T) A.w.cact[par][q] = jmap[L.cact[q]];
-    for (int q = tid; q < nact0; q += T) A.w.cmass[jmap[q]] = L.cmass[q];
+    for (int q = tid; q < nact0; q += T) A.w.cmass[jmap[q]] = fmax(L.cmass[q], 0.0);  // served in full: -f
     __syncthreads();
     if (tid == 0) {
         st->status = status;

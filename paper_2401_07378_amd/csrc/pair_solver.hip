@@ -189,7 +189,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
                     float xc = X[(size_t)i * D + t] - centre[t];
                     r[t] = -2.f * xc;
                     h = fmaf(xc, xc, h);
-                    fq = max(fq, frac_bits(xc));
+                    fq = max(fq, centred_bits(X[(size_t)i * D + t], centre[t], xc));
                     amax = fmaxf(amax, fabsf(xc));
                 }
                 r[D] = h;
@@ -207,7 +207,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 #pragma unroll
                 for (int t = 0; t < D; ++t) {
                     const float yc = L1 ? Y[(size_t)j * D + t] : Y[(size_t)j * D + t] - centre[t];
-                    fq = max(fq, frac_bits(yc));
+                    fq = max(fq, L1 ? frac_bits(yc) : centred_bits(Y[(size_t)j * D + t], centre[t], yc));
                     amax = fmaxf(amax, fabsf(yc));
                 }
             }
@@ -241,18 +241,17 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
         NNSEMD_PH(1)
         NNSEMD_PH(2)
 
-        // ---- 2. claimant sets a_i
-        round_buckets<T>(L, sh, mact, nact);
+        // ---- 2. claimant sets a_i (exact keys leave room for the index)
+        round_buckets_pos<T, CSMAX>(L, sh, mact, nact, exact);
         NNSEMD_PH(3)
         // ---- 3. flow & cost: claimant order, then the serve walk
-        round_rank<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, A.metric,
-                             A.protocol == NNSEMD_GREEDY ? &sh.tie_order : nullptr);
+        round_rank_pos<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, exact);
         NNSEMD_PH(5)
-        round_walk<T, true, true>(L, mact, A.metric, cost);
+        round_walk_pos<T>(L, mact);
         NNSEMD_PH(6)
-        // ---- 4. weights update: plan append + compaction
-        round_compact<T, CSMAX, RS, true>(L, sh, mact, nact, nnz, want_plan ? A.plan_src : nullptr, A.plan_dst,
-                                    A.plan_flow, plan_base);
+        // ---- 4. weights update: cost, plan append, compaction
+        round_compact_pos<T, CSMAX, RS, true>(L, sh, mact, nact, nnz, want_plan ? A.plan_src : nullptr, A.plan_dst,
+                                              A.plan_flow, plan_base, A.metric, A.protocol == NNSEMD_GREEDY, cost);
         NNSEMD_PH(7)
         ++rounds;
     }
@@ -301,7 +300,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX <= 2 &&
 void pair_solver_kernel(PairSolverArgs A) {
     extern __shared__ __align__(16) char lds_dyn[];
     __shared__ SharedCore sh;
-    const Lds16 L = carve16(lds_dyn, A.max_m, A.max_n, record_stride(D), CL ? D : 0, A.share_order != 0);
+    const Lds16 L = carve16(lds_dyn, A.max_m, A.max_n, record_stride(D), CL ? D : 0, true);
     const int64_t p = A.order != nullptr ? (int64_t)A.order[blockIdx.x] : (int64_t)blockIdx.x;
     solve_pair<D, T, CSMAX, L1, CL>(A, p, L, sh);
 }
@@ -404,6 +403,7 @@ template <bool CL>
 int dispatch_cl(bool run, const PairSolverArgs& A, int d, int threads, int chunk_max, size_t lds, int grid,
                 hipStream_t st, int* blocks) {
     if (threads == 256) {
+        if (chunk_max <= 1) return dispatch<256, 1, CL>(run, A, d, lds, grid, st, blocks);
         if (chunk_max <= 4) return dispatch<256, 4, CL>(run, A, d, lds, grid, st, blocks);
         if (chunk_max <= 16) return dispatch<256, 16, CL>(run, A, d, lds, grid, st, blocks);
     } else if (threads == 512) {

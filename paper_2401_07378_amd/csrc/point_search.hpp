@@ -78,6 +78,13 @@ __device__ inline int frac_bits(float v) {
     return q > 0 ? q : 0;
 }
 
+// The same of a centred coordinate xc = fl(x - c), which only counts when the
+// subtraction did not round (a point near zero can lose its low bits to a
+// larger centre and then look like a lattice point).
+__device__ inline int centred_bits(float x, float c, float xc) {
+    return (double)xc + (double)c == (double)x ? frac_bits(xc) : 200;
+}
+
 // Exact-key test.  If every centred coordinate is a multiple of 2^-q with
 // magnitude <= R, every term of a Euclidean key (x^_t^2, 2 x^_t y^_t) is a
 // multiple of 2^-2q and every partial sum is at most 3 D R^2 in magnitude, so

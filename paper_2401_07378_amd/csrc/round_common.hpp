@@ -67,6 +67,8 @@ static_assert(sizeof(double) * kMaxWaves * kMaxReduce == kPairRedBytes, "reducti
 // Shared carries one, the compact point path lends its FP64 key array.
 struct SharedCore {
     unsigned long long scan[kMaxWaves];
+    unsigned btot[kWave];  // per (chunk, wavefront) totals: claimants (round_buckets_pos), later in the
+                           // round the three streams of round_compact_pos, 8 bits each
     unsigned long long tie_nn;     // near-tie counters of the pair (LDS atomics: hits are rare,
     unsigned long long tie_order;  // and no register is held across the rounds for them)
     int32_t nflag;  // near-tie consumers of the search
@@ -131,6 +133,7 @@ __device__ inline bool near_tie_dist(double d1, double d2) {
 // candidates; the decision itself is always the one on distances.
 __device__ inline bool keys_near(double k1, double k2, int metric) {
     if (metric == NNSEMD_L2 && k2 - k1 > 2.1e-6 * k1 + 1e-24) return false;
+    if (k1 == k2) return true;  // equal keys (exact ties are common on lattices): no square roots
     return near_tie_dist(dist_of_key(k1, metric), dist_of_key(k2, metric));
 }
 
@@ -176,6 +179,22 @@ __device__ inline unsigned long long wave_incl_scan_u64(unsigned long long x) {
     x += dpp_u64<0x142, 0xa>(x);  // row_bcast:15
     x += dpp_u64<0x143, 0xc>(x);  // row_bcast:31
     return x;
+}
+
+// The same scan of 32-bit values: one DPP add per step.
+__device__ inline unsigned wave_incl_scan_u32(unsigned x) {
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Number of set bits of a wavefront mask below this lane.
+__device__ inline unsigned mask_rank(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
 // Exclusive block scan of one 64-bit value per thread; *total = block sum.
@@ -490,6 +509,303 @@ __device__ inline void round_compact(const LT& L, SharedCore& sh, int& mact, int
     nnz += (int64_t)(tot & mask);
     mact = (int)((tot >> 21) & mask);
     nact = (int)(tot >> 42);
+    if (tid == 0) sh.nflag = 0;
+    __syncthreads();
+}
+
+// =====================================================================
+// Bucket-major form of the phases after the search (point path, given-D path
+// and the single-workgroup finish).  After the search has stored each active
+// consumer's pick and exact key, the claimants are moved into bucket order
+// together with their keys and slots, so that the order, the walk and the
+// plan append read consecutive LDS words instead of chasing consumer indices:
+//   round_buckets_pos  list[p] = consumer, ckey[p] = key, cnn[p] = slot
+//   round_rank_pos     the same arrays in serve order
+//   round_walk_pos     flows, left in the mass arrays (see there)
+//   round_compact_pos  cost, near ties, plan append, surviving sets
+// Work is dealt in chunks of T consecutive slots (thread t: slots t, t + T,
+// ...), so every LDS access of a wavefront is unit-stride, a wavefront skips
+// the chunks past the active count, and the block prefixes are one ballot or
+// one 32-bit DPP scan per chunk plus one scan over the at most 64
+// (chunk, wavefront) totals that every wavefront takes from LDS by itself.
+// What bounds these phases is issued instructions in batches and the
+// barrier-to-barrier latency for a single pair.  Against the consumer-major
+// form before it (each claimant walked its bucket through two dependent LDS
+// reads per member, all chunks of the largest pair always unrolled, 64-bit
+// packed scans), thousands of cycles per pair, rank phase (whole pair):
+//   256-point clouds, 1000 pairs      137 (396) ->  55 (295), 0.43 -> 0.29 ms
+//   128..1024-point pairs, 4096       84 (440) ->  40 (421), 1.185 -> 1.159 ms
+//   32 x 32 pixel grids, 2048       1245 (2701) -> 451 (2040), 4.28 -> 3.27 ms
+constexpr int kPartialServe = 0x8000;  // cnn[p] flag: served in part, its supplier is exhausted
+
+// Order keys with the consumer index in the low bits of the mantissa: when
+// every key of a launch has at least 12 trailing zero mantissa bits (FP32
+// entries, exact lattice keys), (key, j) order is one FP64 comparison and no
+// two keys are equal.  j < 4096.
+constexpr unsigned long long kPackMask = 0xfffull;
+__device__ inline double pack_key(double k, int j) {
+    return __longlong_as_double(__double_as_longlong(k + 0.0) | (long long)j);  // + 0.0: no negative zero
+}
+__device__ inline double unpack_key(double k) {
+    return __longlong_as_double(__double_as_longlong(k) & ~(long long)kPackMask);
+}
+
+// ---- claimant sets a_i in bucket order.  pack: see pack_key; the keys of
+// buckets with two or more members are left packed for round_rank_pos.
+template <int T, int CS, typename LT>
+__device__ inline void round_buckets_pos(const LT& L, SharedCore& sh, int mact, int nact, bool pack) {
+    constexpr int NW = T / kWave;
+    static_assert(CS * NW <= kWave, "one total per lane");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    unsigned cnt[CS], inc[CS];
+    int jv[CS], sv[CS];
+    double kv[CS];
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        const int s = u * T + tid;
+        cnt[u] = 0u;
+        if (u * T + wave * kWave < mact) cnt[u] = s < mact ? (unsigned)L.scnt[s] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        const int q = u * T + tid;
+        jv[u] = 0;
+        sv[u] = 0;
+        kv[u] = 0.0;
+        if (q < nact) {
+            jv[u] = L.cact[q];
+            sv[u] = L.cnn[jv[u]];
+            kv[u] = L.ckey[jv[u]];
+        }
+    }
+    // two chunks per 32-bit scan: a wavefront's counts sum to at most 4096
+#pragma unroll
+    for (int u = 0; u < CS; u += 2) {
+        const unsigned hi = u + 1 < CS ? cnt[u + 1 < CS ? u + 1 : u] : 0u;
+        unsigned x = 0u;
+        if (u * T + wave * kWave < mact) x = wave_incl_scan_u32(cnt[u] | (hi << 16));
+        inc[u] = x & 0xffffu;
+        if (u + 1 < CS) inc[u + 1 < CS ? u + 1 : u] = x >> 16;
+    }
+    if (lane == kWave - 1) {
+#pragma unroll
+        for (int u = 0; u < CS; ++u) sh.btot[u * NW + wave] = inc[u];
+    }
+    __syncthreads();
+    {
+        const unsigned v = lane < CS * NW ? sh.btot[lane] : 0u;
+        const unsigned ex = wave_incl_scan_u32(v) - v;
+#pragma unroll
+        for (int u = 0; u < CS; ++u) {
+            const int s = u * T + tid;
+            const unsigned base = (unsigned)__builtin_amdgcn_readlane((int)ex, u * NW + wave);
+            if (s < mact) L.soff[s] = (int)(base + inc[u] - cnt[u]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        if (u * T + tid < nact) {
+            const int pos = cnt_add(L.soff, sv[u]);
+            L.list[pos] = jv[u];
+            L.cnn[pos] = sv[u];
+            L.ckey[pos] = pack && L.scnt[sv[u]] > 1 ? pack_key(kv[u], jv[u]) : kv[u];
+        }
+    }
+    __syncthreads();
+}
+
+// ---- serve order inside each bucket: a claimant's rank is the number of
+// members below it, counted over consecutive keys that all members of the
+// bucket read together.
+template <int T, int CS, typename LT>
+__device__ inline void round_rank_pos(const LT& L, int nact, int protocol, uint64_t seed, int rounds, bool pack) {
+    const int tid = threadIdx.x;
+    int np[CS], jv[CS];
+    double kv[CS];
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        const int p = u * T + tid;
+        np[u] = -1;
+        jv[u] = 0;
+        kv[u] = 0.0;
+        if (p >= nact) continue;
+        const int sl = L.cnn[p];
+        const int c = L.scnt[sl];
+        if (c < 2) continue;
+        const int end = L.soff[sl], start = end - c;
+        const int j = L.list[p];
+        const double k = L.ckey[p];
+        int rank = 0;
+        if (protocol == NNSEMD_GREEDY) {
+            int le = 0;
+#pragma unroll 4
+            for (int e = start; e < end; ++e) {
+                const double k2 = L.ckey[e];
+                rank += k2 < k;
+                le += k2 <= k;
+            }
+            if (le - rank > 1) {  // equal keys: by consumer index
+                for (int e = start; e < end; ++e) rank += L.ckey[e] == k && L.list[e] < j;
+            }
+        } else {
+            // the random order is drawn for the caller's consumer indices
+            const uint64_t r = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j] : j);
+#pragma unroll 4
+            for (int e = start; e < end; ++e) {
+                const int j2 = L.list[e];
+                const uint64_t r2 = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j2] : j2);
+                rank += (r2 < r) || (r2 == r && j2 < j);
+            }
+        }
+        np[u] = start + rank;
+        jv[u] = j;
+        kv[u] = pack ? unpack_key(k) : k;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        if (np[u] >= 0) {
+            L.list[np[u]] = jv[u];
+            L.ckey[np[u]] = kv[u];
+        }
+    }
+    __syncthreads();
+}
+
+// ---- flows: one lane per claimed supplier serves its claimants in order
+// while it holds mass.  The chain holds only the masses; flows stay where
+// the masses were: a consumer served in full keeps -f (its mass is gone), and
+// the one served in part (the supplier's last) is flagged in cnn[p] with the
+// supplier's slot keeping -f.  Both read as "not active any more", and the
+// keys stay untouched for the near-tie count and the cost.  `serve` is
+// called for every serve (position, consumer, flow) in order.
+template <int T, typename LT, typename F>
+__device__ inline void walk_supplier(const LT& L, int s, F&& serve) {
+    const int c = L.scnt[s];
+    if (c == 0) return;
+    const int end = L.soff[s];
+    int pos = end - c;
+    double sm = L.smass[s];
+    while (pos < end && sm > 0.0) {
+        const int j = L.list[pos];
+        const double cm = L.cmass[j];
+        const double f = sm < cm ? sm : cm;
+        serve(pos, j, f);
+        if (sm < cm) {
+            L.cmass[j] = cm - f;
+            L.cnn[pos] = s | kPartialServe;
+            sm = -f;
+        } else {
+            L.cmass[j] = -f;
+            sm = sm - f;
+        }
+        ++pos;
+    }
+    L.smass[s] = sm;
+}
+template <int T, typename LT>
+__device__ inline void round_walk_pos(const LT& L, int mact) {
+    for (int s = threadIdx.x; s < mact; s += T) walk_supplier<T>(L, s, [](int, int, double) {});
+    __syncthreads();
+}
+
+// ---- cost and near ties of the round, plan append, compaction of the
+// active sets.  COST: this thread's part of R from the keys.
+template <int T, int CS, int RS, bool COST, typename LT>
+__device__ inline void round_compact_pos(const LT& L, SharedCore& sh, int& mact, int& nact, int64_t& nnz,
+                                         int32_t* plan_src, int32_t* plan_dst, double* plan_flow, int64_t plan_base,
+                                         int metric, bool greedy, double& cost) {
+    constexpr int RSA = RS > 0 ? RS : 4;
+    constexpr int NW = T / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    double pf[CS], smv[CS];
+    int pj[CS], psu[CS], sid[CS], cid[CS];
+    float rec[CS][RSA];
+    unsigned pre[CS];
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        const int p = u * T + tid;
+        unsigned tot = 0u;
+        pre[u] = 0u;
+        pf[u] = 0.0;
+        pj[u] = psu[u] = 0;
+        sid[u] = cid[u] = -1;
+        smv[u] = 0.0;
+        if (u * T + wave * kWave < nact) {
+            bool near = false, alive = false;
+            if (p < nact) {
+                const int raw = L.cnn[p];
+                const int slot = raw & (kPartialServe - 1);
+                const int j = L.list[p];
+                const double cm = L.cmass[j];
+                const double k = L.ckey[p];
+                if (cm < 0.0)
+                    pf[u] = -cm;
+                else if (raw & kPartialServe)
+                    pf[u] = -L.smass[slot];
+                if (greedy && p > 0 && (L.cnn[p - 1] & (kPartialServe - 1)) == slot)
+                    near = keys_near(L.ckey[p - 1], k, metric);
+                if (pf[u] > 0.0) {
+                    if constexpr (COST) cost = cost + pf[u] * dist_of_key(k, metric);
+                    pj[u] = j;
+                    psu[u] = L.sidx[slot];
+                }
+                const int jq = L.cact[p];
+                alive = L.cmass[jq] > 0.0;
+                if (alive) cid[u] = jq;
+            }
+            const unsigned long long nb = __ballot(near);
+            if (nb != 0ull && lane == 0) atomicAdd(&sh.tie_order, (unsigned long long)__popcll(nb));
+            const unsigned long long bp = __ballot(pf[u] > 0.0), bc = __ballot(alive);
+            pre[u] = mask_rank(bp) | (mask_rank(bc) << 16);
+            tot = (unsigned)__popcll(bp) | ((unsigned)__popcll(bc) << 16);
+        }
+        if (u * T + wave * kWave < mact) {
+            bool alive = false;
+            if (p < mact) {
+                smv[u] = L.smass[p];
+                alive = smv[u] > 0.0;
+                if (alive) {
+                    sid[u] = L.sidx[p];
+                    if constexpr (RS > 0) load_rec<RS>(L.srec, p, rec[u]);
+                }
+            }
+            const unsigned long long bs = __ballot(alive);
+            pre[u] |= mask_rank(bs) << 8;
+            tot |= (unsigned)__popcll(bs) << 8;
+        }
+        if (lane == 0) sh.btot[u * NW + wave] = tot;
+    }
+    __syncthreads();
+    const unsigned v = lane < CS * NW ? sh.btot[lane] : 0u;
+    const unsigned va = (v & 0xffu) | ((v & 0xff00u) << 8), vc = v >> 16;
+    const unsigned ia = wave_incl_scan_u32(va), ic = wave_incl_scan_u32(vc);
+#pragma unroll
+    for (int u = 0; u < CS; ++u) {
+        const unsigned ba = (unsigned)__builtin_amdgcn_readlane((int)(ia - va), u * NW + wave);
+        const unsigned bc = (unsigned)__builtin_amdgcn_readlane((int)(ic - vc), u * NW + wave);
+        if (plan_src != nullptr && pf[u] > 0.0) {
+            const int64_t e = plan_base + nnz + (ba & 0xffffu) + (pre[u] & 0xffu);
+            plan_src[e] = psu[u];
+            plan_dst[e] = L.jmap != nullptr ? L.jmap[pj[u]] : pj[u];
+            plan_flow[e] = pf[u];
+        }
+        if (sid[u] >= 0) {
+            const int ws = (int)((ba >> 16) + ((pre[u] >> 8) & 0xffu));
+            if constexpr (RS > 0) store_rec<RS>(L.srec, ws, rec[u]);
+            L.sidx[ws] = sid[u];
+            L.smass[ws] = smv[u];
+            L.scnt[ws] = 0;
+        }
+        if (cid[u] >= 0) L.cact[bc + (pre[u] >> 16)] = cid[u];
+    }
+    const unsigned ta = (unsigned)__builtin_amdgcn_readlane((int)ia, kWave - 1);
+    nnz += (int64_t)(ta & 0xffffu);
+    mact = (int)(ta >> 16);
+    nact = __builtin_amdgcn_readlane((int)ic, kWave - 1);
     if (tid == 0) sh.nflag = 0;
     __syncthreads();
 }

@@ -1,0 +1,80 @@
+"""Edges of the bucket-major round phases of the point and given-D paths:
+active counts at the wavefront and workgroup-chunk boundaries, one supplier
+with every consumer in its bucket, exact ties inside buckets (packed and
+unpacked order keys), partial serves, and the lattice test on coordinates
+that the centring would round.  Plans and counters must equal the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2401_07378_amd import workloads as W
+from tests.gpu_helpers import assert_pair_matches, gpu_pair, oracle_pair, to_dev
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [(1, 1), (1, 300), (300, 1), (63, 65), (64, 64), (65, 63), (255, 257), (256, 256), (257, 255), (512, 513),
+         (769, 1023), (1024, 1024), (1025, 900)]
+
+
+@pytest.mark.parametrize("mn", EDGES, ids=lambda v: "%dx%d" % v)
+@pytest.mark.parametrize("lattice", [0, 5])
+@pytest.mark.parametrize("protocol", ["greedy", "random"])
+def test_chunk_edges(mn, lattice, protocol):
+    m, n = mn
+    X, a, Y, b = W.random_pair(900 + m + 3 * n + lattice, m, n, 3, masses="integer" if lattice else "dirichlet",
+                               lattice=lattice)
+    for threads in (256, 512):
+        g = gpu_pair(X, a, Y, b, protocol=protocol, seed=3, threads=threads)
+        assert_pair_matches(g, oracle_pair(X, a, Y, b, protocol=protocol, seed=3), label=f"{mn}-{lattice}-{threads}")
+
+
+@pytest.mark.parametrize("metric", ["l2", "sqeuclidean", "l1"])
+def test_one_hub_supplier(metric):
+    """Every consumer's nearest supplier is the same one, on an integer ring
+    of equal distances: one bucket holds all claimants, tied."""
+    rng = np.random.default_rng(17)
+    Y = np.concatenate([rng.integers(0, 3, size=(700, 2)), [[1, 1]]]).astype(np.float32)
+    X = np.concatenate([[[1, 1]], 60 + rng.integers(0, 9, size=(200, 2))]).astype(np.float32)
+    b = np.full(len(Y), 1.0 / len(Y), np.float32)
+    a = np.full(len(X), 1.0 / len(X), np.float32)
+    assert_pair_matches(gpu_pair(X, a, Y, b, metric), oracle_pair(X, a, Y, b, metric), label=metric)
+
+
+def test_centre_that_hides_low_bits():
+    """Points at 0 and 2^-30 next to points at 1: both centre to -0.5 in
+    FP32, so the pair looks like a lattice but its keys are not exact."""
+    t = np.float32(2.0 ** -30)
+    X = np.array([[0.0], [t], [1.0]] * 20, np.float32)
+    Y = np.array([[t], [0.0], [1.0]] * 20, np.float32)
+    a = np.full(60, 1.0 / 60, np.float32)
+    g = gpu_pair(X, a, Y, a, "l1")
+    assert_pair_matches(g, oracle_pair(X, a, Y, a, "l1"), label="l1")
+    g = gpu_pair(X, a, Y, a, "l2")
+    assert_pair_matches(g, oracle_pair(X, a, Y, a, "l2"), label="l2")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("mn", [(1, 400), (257, 255), (513, 1024), (1500, 1300)], ids=lambda v: "%dx%d" % v)
+def test_given_d_ties(mn, dtype):
+    """Small integer distances (zeros of both signs among them): ties in
+    every bucket, order keys packed for FP32 and compared in full for FP64."""
+    import torch
+    from paper_2401_07378_amd import binding
+    m, n = mn
+    rng = np.random.default_rng(m + n)
+    D = rng.integers(0, 6, size=(m, n)).astype(dtype)
+    D[(D == 0) & (rng.random((m, n)) < 0.5)] = -0.0
+    a = W.dirichlet_masses(rng, m)
+    b = W.dirichlet_masses(rng, n)
+    r = binding.emd_approx_cost(to_dev(D), to_dev(a), to_dev(b))
+    torch.cuda.synchronize()
+    st = binding.stats_numpy(r["stats"])[0]
+    ref = oracle.solve_cost(np.abs(D), a, b)
+    k = int(st["nnz"])
+    assert st["status"] == 0 and k == ref["nnz"] and int(st["rounds"]) == ref["rounds"]
+    assert np.array_equal(r["plan_src"][:k].cpu().numpy(), ref["src"])
+    assert np.array_equal(r["plan_dst"][:k].cpu().numpy(), ref["dst"])
+    assert np.array_equal(r["plan_flow"][:k].cpu().numpy(), ref["flow"])
+    assert int(st["near_ties_nn"]) == ref["near_ties_nn"]
+    assert int(st["near_ties_order"]) == ref["near_ties_order"]
+    assert float(r["cost"].item()) == pytest.approx(ref["cost"], rel=1e-12)
