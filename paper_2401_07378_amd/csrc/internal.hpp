@@ -51,13 +51,13 @@ struct PairSolverArgs {
 
 // Byte layout of the dynamic LDS of one workgroup (one pair at a time).
 struct PairLdsLayout {
-    size_t smass, cmass, ckey, srec, sidx, scnt, soff, cact, cnn, list, sorted, xl, yl, total;
+    size_t smass, cmass, ckey, srec, sidx, scnt, soff, cact, cnn, list, sorted, yl, total;
 };
 
 __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// cd > 0: also the pair's coordinates, cd floats per point (suppliers then
-// consumers, by local index), so the rounds never read them from HBM.
+// cd > 0: also the consumers' coordinates, cd floats per point by local index,
+// so the rounds never read them from HBM.
 // compact (point path): 16-bit index arrays (even lengths, 4-byte aligned,
 // so a packed 32-bit counter atomic stays inside its array) and the FP64 key
 // array at least kPairRedBytes long: it is the block reductions' scratch
@@ -90,7 +90,6 @@ __host__ __device__ inline PairLdsLayout pair_lds_layout(int M, int N, int rs, i
         L.sorted = o; o += isz * Ne;
     }
     o = align_up(o, 16);
-    L.xl = o;    o += sizeof(float) * (size_t)cd * (size_t)M;
     L.yl = o;    o += sizeof(float) * (size_t)cd * (size_t)N;
     L.total = align_up(o, 16);
     return L;

@@ -1252,6 +1252,9 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
 #pragma unroll
         for (int q = 0; q < RS / 4; ++q) dst[q] = src[q];
         L.sidx[s] = A.w.sidx[par][s];
+        // the finish's records hold the coordinates as given (key32)
+#pragma unroll
+        for (int t = 0; t < D; ++t) L.srec[(size_t)s * RS + t] = A.X[(int64_t)A.w.sidx[par][s] * D + t];
         L.smass[s] = A.w.smass[par][s];
         L.scnt[s] = 0;
     }
@@ -1275,7 +1278,7 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
             break;
         }
         work += (int64_t)mact * nact;
-        near += ps::search_round<D, T, kLpTailChunk, L1>(L, sh, A.X, Yt, centre, rhat, mact, nact, 1, false,
+        near += ps::search_round<D, T, kLpTailChunk, L1>(L, sh, Yt, centre, rhat, mact, nact, 1, false,
                                                           A.metric);
         rc::round_buckets_pos<T, kLpTailChunk>(L, sh, mact, nact, false);
         rc::round_rank_pos<T, kLpTailChunk>(L, nact, A.protocol, A.seed, (int)rounds, false);

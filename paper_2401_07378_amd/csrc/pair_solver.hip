@@ -36,8 +36,9 @@ namespace {
 using namespace rc;
 using namespace ps;
 
-// CL: the pair's coordinates are copied into LDS at ingest (L.xl, L.yl) and
-// every later read takes them from there; otherwise from HBM.
+// CL: the consumers' coordinates are copied into LDS at ingest (L.yl) and
+// every later read takes them from there; otherwise from HBM (the suppliers'
+// are in their search records either way).
 template <int D, int T, int CSMAX, bool L1, bool CL>
 __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, SharedCore& sh) {
     constexpr int RS = record_stride(D);
@@ -88,8 +89,8 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
     const float* __restrict__ Xg = A.X + x0 * D;
     const float* __restrict__ Yg = A.Y + y0 * D;
     const int mi = (int)m, ni = (int)n;
-    // coordinates for the rounds (LDS copies in the CL variant, filled below)
-    const float* __restrict__ X = CL ? L.xl : Xg;
+    // consumer coordinates for the rounds (LDS copies in the CL variant, filled below)
+    const float* __restrict__ X = Xg;
     const float* __restrict__ Y = CL ? L.yl : Yg;
 
     // ------------------------------------- ingest: masses, checks, bounding box
@@ -111,7 +112,6 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 #pragma unroll
         for (int t = 0; t < D; ++t) {
             float xv = Xg[(size_t)i * D + t];
-            if constexpr (CL) L.xl[(size_t)i * D + t] = xv;
             if (!isfinite(xv)) red[2] = 1.0;
             red[3 + t] = fmin(red[3 + t], (double)xv);
             red[3 + D + t] = fmax(red[3 + D + t], (double)xv);
@@ -187,7 +187,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 #pragma unroll
                 for (int t = 0; t < D; ++t) {
                     float xc = X[(size_t)i * D + t] - centre[t];
-                    r[t] = -2.f * xc;
+                    r[t] = X[(size_t)i * D + t];
                     h = fmaf(xc, xc, h);
                     fq = max(fq, centred_bits(X[(size_t)i * D + t], centre[t], xc));
                     amax = fmaxf(amax, fabsf(xc));
@@ -236,7 +236,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 
         // ---- 1. NNS: FP32 scan, best + second best, near ties deferred
         // and re-scored in FP64; each pick counted into its bucket.
-        near += ps::search_round<D, T, CSMAX, L1>(L, sh, X, Y, centre, rhat, mact, nact, A.split, exact,
+        near += ps::search_round<D, T, CSMAX, L1>(L, sh, Y, centre, rhat, mact, nact, A.split, exact,
                                                    A.metric);
         NNSEMD_PH(1)
         NNSEMD_PH(2)
@@ -296,7 +296,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 // whose larger LDS records hold a 1024-point pair to two or three
 // workgroups per CU anyway.
 template <int D, int T, int CSMAX, bool L1, bool CL>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX <= 2 && D <= 3 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
 void pair_solver_kernel(PairSolverArgs A) {
     extern __shared__ __align__(16) char lds_dyn[];
     __shared__ SharedCore sh;

@@ -51,7 +51,6 @@ struct LdsT {
     I* cnn;         // [N] pick (active slot) by consumer; after the serve: supplier local index
     I* list;        // [N] near-tie consumers during the search; claimant buckets after
     I* sorted;      // [N] claimant buckets in serve order (the list's storage when compact)
-    float* xl;      // [M * cd] supplier coordinates by local index (coordinate variant only)
     float* yl;      // [N * cd] consumer coordinates by local index (coordinate variant only)
     const int32_t* jmap;  // [N] caller's consumer index of each local one (null: the same)
 };
@@ -92,7 +91,6 @@ __device__ inline LdsT<I> carve_t(char* base, const PairLdsLayout& L) {
     s.cnn = reinterpret_cast<I*>(base + L.cnn);
     s.list = reinterpret_cast<I*>(base + L.list);
     s.sorted = reinterpret_cast<I*>(base + L.sorted);
-    s.xl = reinterpret_cast<float*>(base + L.xl);
     s.yl = reinterpret_cast<float*>(base + L.yl);
     s.jmap = nullptr;
     return s;
@@ -735,31 +733,29 @@ __device__ inline void round_compact_pos(const LT& L, SharedCore& sh, int& mact,
         sid[u] = cid[u] = -1;
         smv[u] = 0.0;
         if (u * T + wave * kWave < nact) {
-            bool near = false, alive = false;
-            if (p < nact) {
-                const int raw = L.cnn[p];
-                const int slot = raw & (kPartialServe - 1);
-                const int j = L.list[p];
-                const double cm = L.cmass[j];
-                const double k = L.ckey[p];
-                if (cm < 0.0)
-                    pf[u] = -cm;
-                else if (raw & kPartialServe)
-                    pf[u] = -L.smass[slot];
-                if (greedy && p > 0 && (L.cnn[p - 1] & (kPartialServe - 1)) == slot)
-                    near = keys_near(L.ckey[p - 1], k, metric);
-                if (pf[u] > 0.0) {
-                    if constexpr (COST) cost = cost + pf[u] * dist_of_key(k, metric);
-                    pj[u] = j;
-                    psu[u] = L.sidx[slot];
-                }
-                const int jq = L.cact[p];
-                alive = L.cmass[jq] > 0.0;
-                if (alive) cid[u] = jq;
-            }
-            const unsigned long long nb = __ballot(near);
+            // every first-level read is issued before any is used, then the
+            // reads behind them: two LDS latencies per chunk, no branches
+            const int pc = min(p, nact - 1);
+            const int pp = max(pc - 1, 0);
+            const int raw = L.cnn[pc], rawp = L.cnn[pp];
+            const int j = L.list[pc], jq = L.cact[pc];
+            const double k = L.ckey[pc], kp = L.ckey[pp];
+            const int slot = raw & (kPartialServe - 1);
+            const double cm = L.cmass[j], cq = L.cmass[jq], sm = L.smass[slot];
+            psu[u] = L.sidx[slot];
+            pj[u] = j;
+            const bool in = p < nact;
+            const double f = cm < 0.0 ? -cm : ((raw & kPartialServe) != 0 ? -sm : 0.0);
+            pf[u] = in ? f : 0.0;
+            const bool alive = in && cq > 0.0;
+            if (alive) cid[u] = jq;
+            const bool nb1 = greedy && in && p > 0 && (rawp & (kPartialServe - 1)) == slot;
+            bool near = false;
+            if (__ballot(nb1) != 0ull) near = nb1 && keys_near(kp, k, metric);
+            const unsigned long long bp = __ballot(pf[u] > 0.0), bc = __ballot(alive), nb = __ballot(near);
+            if constexpr (COST)
+                if (bp != 0ull) cost = cost + pf[u] * dist_of_key(k, metric);
             if (nb != 0ull && lane == 0) atomicAdd(&sh.tie_order, (unsigned long long)__popcll(nb));
-            const unsigned long long bp = __ballot(pf[u] > 0.0), bc = __ballot(alive);
             pre[u] = mask_rank(bp) | (mask_rank(bc) << 16);
             tot = (unsigned)__popcll(bp) | ((unsigned)__popcll(bc) << 16);
         }
@@ -780,6 +776,9 @@ __device__ inline void round_compact_pos(const LT& L, SharedCore& sh, int& mact,
         if (lane == 0) sh.btot[u * NW + wave] = tot;
     }
     __syncthreads();
+    int32_t* const psrc = plan_src != nullptr ? plan_src + plan_base + nnz : nullptr;  // uniform
+    int32_t* const pdst = plan_dst + plan_base + nnz;
+    double* const pflw = plan_flow + plan_base + nnz;
     const unsigned v = lane < CS * NW ? sh.btot[lane] : 0u;
     const unsigned va = (v & 0xffu) | ((v & 0xff00u) << 8), vc = v >> 16;
     const unsigned ia = wave_incl_scan_u32(va), ic = wave_incl_scan_u32(vc);
@@ -787,11 +786,11 @@ __device__ inline void round_compact_pos(const LT& L, SharedCore& sh, int& mact,
     for (int u = 0; u < CS; ++u) {
         const unsigned ba = (unsigned)__builtin_amdgcn_readlane((int)(ia - va), u * NW + wave);
         const unsigned bc = (unsigned)__builtin_amdgcn_readlane((int)(ic - vc), u * NW + wave);
-        if (plan_src != nullptr && pf[u] > 0.0) {
-            const int64_t e = plan_base + nnz + (ba & 0xffffu) + (pre[u] & 0xffu);
-            plan_src[e] = psu[u];
-            plan_dst[e] = L.jmap != nullptr ? L.jmap[pj[u]] : pj[u];
-            plan_flow[e] = pf[u];
+        if (psrc != nullptr && pf[u] > 0.0) {
+            const unsigned e = (ba & 0xffffu) + (pre[u] & 0xffu);
+            psrc[e] = psu[u];
+            pdst[e] = L.jmap != nullptr ? L.jmap[pj[u]] : pj[u];
+            pflw[e] = pf[u];
         }
         if (sid[u] >= 0) {
             const int ws = (int)((ba >> 16) + ((pre[u] >> 8) & 0xffu));
