@@ -267,3 +267,24 @@ def test_retrieval_recall_and_gain():
     print(f"recall@10 trained {r_tr:.4f}, untrained {r_0:.4f}")
     assert r_tr >= 0.99, (r_tr, r_0)
     assert r_tr - r_0 >= 0.1, (r_tr, r_0)
+
+
+@pytest.mark.parametrize("sizes", [[1, 0, 64], [63, 65, 128, 129], [0, 0, 200] + [7] * 600 + [0]],
+                         ids=["edges", "chunks", "many"])
+def test_embed_chunk_edges(sizes):
+    """Sets that end at, before and after a 64-point chunk, empty ones (zero
+    rows, whatever the biases), and more sets than resident workgroups.
+    Bound: FP32 accumulation, and layer-1 values that round to BF16 the other
+    way (2^-8 of one of 256 products)."""
+    from paper_2401_07378_amd import binding
+    r = np.random.default_rng(len(sizes))
+    off = np.zeros(len(sizes) + 1, np.int64)
+    off[1:] = np.cumsum(sizes)
+    X = W.to_f32(r.random((off[-1], 3)))
+    a = np.concatenate([W.dirichlet_masses(r, k) for k in sizes if k]).astype(np.float32)
+    th = _theta(3, bias=0.3)
+    E = binding.sg_embed(to_dev(th), to_dev(X), to_dev(a), to_dev(off)).cpu().numpy()
+    want = SO.embed(th, X, a, off, rounding=True)
+    assert np.abs(E - want).max() <= 1e-3 * np.abs(want).max()
+    for s, k in enumerate(sizes):
+        assert k > 0 or not E[s].any()
