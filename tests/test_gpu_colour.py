@@ -57,3 +57,19 @@ def test_colour_transfer_onto_itself():
     assert float(g["cost"][0]) == 0.0 and int(g["stats"]["rounds"]) == 1
     want = oracle.colour_transfer(img.reshape(-1, 3), img.reshape(-1, 3), 32, 32, 5)
     np.testing.assert_array_equal(g["image"].reshape(-1, 3), want["image"])
+
+
+@pytest.mark.parametrize("pixels,k,levels", [(1, 1, 256), (63, 15, 256), (64, 16, 4), (65, 17, 3), (1025, 1, 2),
+                                             (4097, 1024, 256), (3000, 255, 5)])
+def test_palette_edges(pixels, k, levels):
+    """Palette sizes around the 16-centroid blocks, pixel counts around the
+    64-pixel groups, and few colour levels (equal centroids and equidistant
+    pixels: ties that the FP32 scan leaves to the FP64 comparison)."""
+    r = np.random.default_rng(pixels + k)
+    ref = (r.integers(0, levels, size=(pixels, 3)) * (255 // (levels - 1))).astype(np.uint8)
+    src = (r.integers(0, levels, size=(pixels, 3)) * (255 // (levels - 1))).astype(np.uint8)
+    g = _run(ref, src, k, k, 3)
+    want = oracle.colour_transfer(ref, src, k, k, 3, "l2")
+    for f in ("ref_palette", "ref_mass", "src_palette", "src_mass", "assign"):
+        np.testing.assert_array_equal(g[f], want[f])
+    np.testing.assert_array_equal(g["image"].reshape(-1, 3), want["image"])
