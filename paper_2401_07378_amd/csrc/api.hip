@@ -1561,34 +1561,24 @@ nnsemd_status_t nnsemd_sg_predict(nnsemd_handle_t h, const float* theta, const f
 }
 
 namespace {
-// Carve the training workspace for B pairs and P points; returns bytes
+// Carve the training workspace for B pairs; returns bytes
 // needed (base == nullptr: size only).
-static size_t sg_train_carve(char* base, int64_t B, int64_t P, bool own_grad, sg::SgTrainWork& w, float** grad) {
+static size_t sg_train_carve(char* base, int64_t B, bool own_grad, sg::SgTrainWork& w, float** grad) {
     constexpr int64_t Hd = kSgHidden;
-    const int64_t Ppad = (P + 63) / 64 * 64, Bpad = (B + 63) / 64 * 64, S = 2 * B;
-    const int64_t nblk = std::max<int64_t>(1, (P + 511) / 512);
+    const int64_t Bpad = (B + 63) / 64 * 64, S = 2 * B;
     Carver c;
-    const size_t oH1 = c.take(2 * Ppad * Hd), oH1T = c.take(2 * Ppad * Hd);
-    const size_t odP = c.take(2 * Ppad * Hd), odPT = c.take(2 * Ppad * Hd);
-    const size_t oPRE2 = c.take(4 * Ppad * Hd), odH1 = c.take(4 * Ppad * Hd);
     const size_t oE = c.take(4 * S * Hd), odE = c.take(4 * S * Hd);
     const size_t oZ = c.take(2 * Bpad * 3 * Hd), oZT = c.take(2 * Bpad * 3 * Hd);
     const size_t odG = c.take(2 * Bpad * Hd), odGT = c.take(2 * Bpad * Hd);
     const size_t oPRE3 = c.take(4 * Bpad * Hd), odZ = c.take(4 * Bpad * 3 * Hd);
     const size_t oHB = c.take(4 * Bpad * kSgHbCols), ohs = c.take(4 * kSgHbCols);
-    const size_t ot = c.take(4 * Bpad), opred = c.take(4 * Bpad), odb2 = c.take(4 * S * Hd);
-    const size_t osplit = c.take(4 * 64 * Hd * Hd), ol1p = c.take(4 * nblk * 4 * Hd), ol1s = c.take(4 * 4 * Hd);
+    const size_t ot = c.take(4 * Bpad), opred = c.take(4 * Bpad);
+    const size_t opart = c.take(4 * (size_t)std::min<int64_t>(S, 256) * kSgTrainPart);
     const size_t obad = c.take(64);
     const size_t ograd = own_grad ? c.take(4 * kSgParams) : 0;
     if (base != nullptr) {
         auto F = [&](size_t o) { return reinterpret_cast<float*>(base + o); };
         auto U = [&](size_t o) { return reinterpret_cast<uint16_t*>(base + o); };
-        w.H1q = U(oH1);
-        w.H1qT = U(oH1T);
-        w.dP2q = U(odP);
-        w.dP2qT = U(odPT);
-        w.PRE2 = F(oPRE2);
-        w.dH1 = F(odH1);
         w.E = F(oE);
         w.dE = F(odE);
         w.Z = U(oZ);
@@ -1601,10 +1591,7 @@ static size_t sg_train_carve(char* base, int64_t B, int64_t P, bool own_grad, sg
         w.hsum = F(ohs);
         w.t = F(ot);
         w.pred = F(opred);
-        w.db2p = F(odb2);
-        w.split = F(osplit);
-        w.l1p = F(ol1p);
-        w.l1s = F(ol1s);
+        w.part = F(opart);
         w.bad = reinterpret_cast<int*>(base + obad);
         if (own_grad) *grad = F(ograd);
     }
@@ -1622,9 +1609,9 @@ static nnsemd_status_t sg_loss_grad_common(nnsemd_handle_t h, const float* theta
     if (s != NNSEMD_OK) return s;
     sg::SgTrainWork w;
     const bool own = *grad == nullptr;
-    const size_t need = sg_train_carve(nullptr, num_pairs, num_points, own, w, grad);
+    const size_t need = sg_train_carve(nullptr, num_pairs, own, w, grad);
     if ((s = sg_workspace(h, need)) != NNSEMD_OK) return s;
-    sg_train_carve(h->sg_ws, num_pairs, num_points, own, w, grad);
+    sg_train_carve(h->sg_ws, num_pairs, own, w, grad);
     const int err = sg::launch_loss_grad(theta, q, X, a, set_off, num_pairs, num_points, labels, w, loss, *grad, stream);
     if (err != 0) return device_fail(h, err, "surrogate backward");
     return NNSEMD_OK;

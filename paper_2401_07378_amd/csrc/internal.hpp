@@ -258,6 +258,7 @@ constexpr int64_t kSgW4 = kSgB3 + kSgHidden;
 constexpr int64_t kSgB4 = kSgW4 + kSgHidden;
 constexpr int64_t kSgParams = kSgB4 + 1;
 constexpr int kSgHbCols = 2 * kSgHidden + 8;  // head-backward row: dg | dt*g | dt | r^2/B | pad
+constexpr int kSgTrainPart = kSgHidden * kSgHidden + 5 * kSgHidden;  // partial gradient of the point layers
 constexpr int kSgTopkMax = 1024;
 
 namespace sg {
@@ -275,16 +276,15 @@ struct SgPredictWork {
     float* PRE3;  // B x H
 };
 struct SgTrainWork {
-    uint16_t *H1q, *H1qT, *dP2q, *dP2qT;  // Ppad x H and H x Ppad
-    float *PRE2, *dH1;                    // P x H
     float *E, *dE;                        // 2B x H
     uint16_t *Z, *ZT, *dGq, *dGqT;        // Bpad x 3H, 3H x Bpad, Bpad x H, H x Bpad
-    float *PRE3, *dZ, *HB, *hsum, *t, *pred, *db2p, *split, *l1p, *l1s;
+    float *PRE3, *dZ, *HB, *hsum, *t, *pred;
+    float* part;                          // min(2B, 256) partial gradients of the point layers
     int* bad;  // offsets check
 };
 int launch_prepare(const float* theta, const SgQuant& q, void* stream);
 int launch_embed(const float* theta, const SgQuant& q, const float* X, const float* a, const int64_t* set_off,
-                 int64_t num_sets, int64_t num_points, float* E, void* stream);
+                 int64_t num_sets, int64_t num_points, float* E, void* stream, bool in_order = false);
 int launch_predict(const float* theta, const SgQuant& q, const float* Eq, int64_t nq, const float* Ec, int64_t nc,
                    const int32_t* qi, const int32_t* ci, int train_layout, int64_t B, const SgPredictWork& w,
                    float* t_out, float* pred, void* stream);

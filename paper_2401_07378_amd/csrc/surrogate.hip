@@ -145,16 +145,6 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t* __restrict
             }
 }
 
-// out[i] = sum_z parts[z * stride + i], z ascending.
-__global__ void sum_splits_kernel(const float* __restrict__ parts, int splits, int64_t stride, float* __restrict__ out,
-                                  int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int z = 0; z < splits; ++z) s += parts[(int64_t)z * stride + i];
-        out[i] = s;
-    }
-}
-
 // out[j] (+)= sum over rows r of in[r * ld + j] (j < cols): 16 row slices
 // per column (rows r = slice mod 16, ascending), then the slices in order.
 constexpr int kColsumThreads = 1024;
@@ -200,18 +190,6 @@ __device__ inline float layer1_pre(const float* __restrict__ x, const float* __r
     return fmaf(x[2], W1q[3 * j + 2], fmaf(x[1], W1q[3 * j + 1], fmaf(x[0], W1q[3 * j], b1[j])));
 }
 
-// H1q[p][j] = bf16(relu(W1 x_p + b1)) for p < P, zero rows up to Ppad.
-__global__ __launch_bounds__(256) void layer1_kernel(const float* __restrict__ X, int64_t P, int64_t Ppad,
-                                                     const float* __restrict__ W1q, const float* __restrict__ b1,
-                                                     uint16_t* __restrict__ H1q) {
-    const int j = threadIdx.x;
-    for (int64_t p = blockIdx.x; p < Ppad; p += gridDim.x) {
-        float h = 0.f;
-        if (p < P) h = fmaxf(layer1_pre(X + 3 * p, W1q, b1, j), 0.f);
-        H1q[p * H + j] = f2bf(h);
-    }
-}
-
 // Point range of set s clamped to [0, P) (offsets are caller data; bad
 // offsets make the loss NaN, never an access outside the buffers).
 __device__ inline void set_range(const int64_t* __restrict__ off, int64_t s, int64_t P, int64_t& lo, int64_t& hi) {
@@ -228,19 +206,6 @@ __global__ void check_offsets_kernel(const int64_t* __restrict__ off, int64_t S,
         if (off[s + 1] < off[s]) bad = 1;
     __syncthreads();
     if (threadIdx.x == 0) *flag = bad;
-}
-
-// E[s][j] = sum_{p in s} a_p relu(PRE2[p][j] + b2[j]), p ascending.
-__global__ __launch_bounds__(256) void pool_kernel(const float* __restrict__ PRE2, const float* __restrict__ b2,
-                                                   const float* __restrict__ a, const int64_t* __restrict__ off,
-                                                   int64_t P, float* __restrict__ E) {
-    const int s = blockIdx.x, j = threadIdx.x;
-    const float bj = b2[j];
-    int64_t lo, hi;
-    set_range(off, s, P, lo, hi);
-    float acc = 0.f;
-    for (int64_t p = lo; p < hi; ++p) acc = fmaf(a[p], fmaxf(PRE2[p * H + j] + bj, 0.f), acc);
-    E[(int64_t)s * H + j] = acc;
 }
 
 // Two non-NaN FP32 values to BF16, round to nearest even (one instruction).
@@ -295,6 +260,11 @@ __device__ inline void layer1_tile(const float4* xs, int np, const float (&w)[2]
 // the two.  Index of 100000 clouds of 256 points (3.39 TFLOP):
 // 6.72 -> 3.72 ms, 913 TFLOP/s, same bits (before: one workgroup per set, W2
 // read from L2 every chunk, BF16 conversion in integer instructions).
+// SEQ: the points of a set are added one after the other in index order (the
+// training forward's definition; its BF16 pair features would otherwise round
+// some values the other way): the sum passes through the four 16-lane groups
+// of a block in row order.
+template <bool SEQ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void embed_fused_kernel(
     const float* __restrict__ X, const float* __restrict__ a, const int64_t* __restrict__ off, int64_t S, int64_t P,
     SgQuant q, const float* __restrict__ theta, float* __restrict__ E) {
@@ -358,20 +328,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void e
                     acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2[k][b], acc[i][b], 0, 0, 0);
             }
         }
-        float part[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (SEQ) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i) {
+                float v[4][4], am[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float am = xs[buf][16 * i + 4 * (lane >> 4) + r].w;
+                for (int r = 0; r < 4; ++r) {
+                    am[r] = xs[buf][16 * i + 4 * (lane >> 4) + r].w;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) part[b] = fmaf(am, fmaxf(acc[i][b][r] + b2v[b], 0.f), part[b]);
+                    for (int b = 0; b < 4; ++b) v[b][r] = fmaxf(acc[i][b][r] + b2v[b], 0.f);
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        float s4 = colsum[b];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) s4 = fmaf(am[r], v[b][r], s4);
+                        colsum[b] = __shfl(s4, 16 * g + r16);
+                    }
             }
+        } else {
+            float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            part[b] += __shfl_xor(part[b], 16);
-            part[b] += __shfl_xor(part[b], 32);
-            colsum[b] += part[b];
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float am = xs[buf][16 * i + 4 * (lane >> 4) + r].w;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) part[b] = fmaf(am, fmaxf(acc[i][b][r] + b2v[b], 0.f), part[b]);
+                }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                part[b] += __shfl_xor(part[b], 16);
+                part[b] += __shfl_xor(part[b], 32);
+                colsum[b] += part[b];
+            }
         }
         if (ends) {
 #pragma unroll
@@ -613,48 +605,216 @@ __global__ void dz_to_de_kernel(const float* __restrict__ dZ, const float* __res
     }
 }
 
-// dPRE2[p][j] = a_p dE[s][j] where PRE2 + b2 > 0 (BF16), and the per-set
-// column sums (FP32, p ascending) for db2.
-__global__ __launch_bounds__(256) void pool_bwd_kernel(const float* __restrict__ PRE2, const float* __restrict__ b2,
-                                                       const float* __restrict__ a, const int64_t* __restrict__ off,
-                                                       int64_t P, const float* __restrict__ dE,
-                                                       uint16_t* __restrict__ dP2q, float* __restrict__ db2_part) {
-    const int s = blockIdx.x, j = threadIdx.x;
-    const float bj = b2[j];
-    const float de = dE[(int64_t)s * H + j];
-    int64_t lo, hi;
-    set_range(off, s, P, lo, hi);
-    float acc = 0.f;
-    for (int64_t p = lo; p < hi; ++p) {
-        const float v = PRE2[p * H + j] + bj > 0.f ? a[p] * de : 0.f;
-        acc += v;
-        dP2q[p * H + j] = f2bf(v);
+// Backward of pooling and both point layers, fused: persistent workgroups walk
+// the 64-point chunks of their sets.  Per chunk, everything stays on chip:
+//   layer 1 again into LDS (BF16), in point-major and unit-major order;
+//   PRE2 = H1 W2^T again on the matrix cores (same products in the same order
+//   as the forward), dP2 = a dE where PRE2 + b2 > 0, rounded to BF16 into LDS
+//   in both orders, its FP32 column sums for db2;
+//   dH1 = dP2 W2 (FP32 in registers), masked by layer 1 and summed with (x, 1);
+//   dW2 += dP2^T H1: each of the 8 wavefronts keeps a 64 x 128 part of the
+//   256 x 256 sum in registers over all its chunks.
+// One partial gradient per workgroup, summed by train_reduce_kernel in order.
+// Before, PRE2, dP2, dH1 and two transposes went through memory (about 1.5 KB
+// a point each way) in nine launches.  Bound: matrix pipe and the W2 / W2^T
+// fragments from L2 (256 KB a chunk).  A step of 512 pairs of 256-point
+// clouds: 1783 -> 434 us.
+constexpr int kTrainThreads = 512;
+constexpr int kTrainGrid = 256;  // one workgroup per CU (its LDS)
+constexpr int kTrainLd = H + 8, kTrainLdT = 64 + 8;
+constexpr size_t kTrainLds = 2 * sizeof(uint16_t) * (64 * (size_t)kTrainLd + H * (size_t)kTrainLdT);
+// partial: dW2 (H x H), dW1 (H x 3), db1 (H), db2 (H)
+constexpr int kTrainPart = kSgTrainPart;
+__global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2))) void train_bwd_kernel(
+    const float* __restrict__ X, const float* __restrict__ a, const int64_t* __restrict__ off, int64_t S, int64_t P,
+    SgQuant q, const float* __restrict__ theta, const float* __restrict__ dE, float* __restrict__ part) {
+    extern __shared__ __align__(16) uint16_t lds16[];
+    uint16_t* h1 = lds16;
+    uint16_t* dp = h1 + 64 * kTrainLd;
+    uint16_t* h1T = dp + 64 * kTrainLd;
+    uint16_t* dpT = h1T + H * kTrainLdT;
+    __shared__ float4 xs[2][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, g4 = lane >> 4, kq = 8 * g4;
+    const int unit = tid & (H - 1), ph = 32 * (tid >> 8);  // layer 1: one unit, 32 points
+    const float* b1 = theta + kSgB1;
+    const float* b2 = theta + kSgB2;
+    const float u0 = q.W1[3 * unit], u1 = q.W1[3 * unit + 1], u2 = q.W1[3 * unit + 2], ub = b1[unit];
+    int colv[2];
+    float b2v[2], w1c[2][4];  // this lane's columns of the products
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int c = 32 * wave + 16 * b + r16;
+        colv[b] = c;
+        b2v[b] = b2[c];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w1c[b][k] = q.W1[3 * c + k];
+        w1c[b][3] = b1[c];
     }
-    db2_part[(int64_t)s * H + j] = acc;
-}
-
-// Partial sums over a chunk of points of dpre1 * [x, 1] (dW1, db1).
-__global__ __launch_bounds__(256) void layer1_bwd_kernel(const float* __restrict__ dH1, const float* __restrict__ X,
-                                                         const float* __restrict__ W1q, const float* __restrict__ b1,
-                                                         int64_t P, int64_t chunk, float* __restrict__ part) {
-    const int j = threadIdx.x;
-    const int64_t lo = blockIdx.x * chunk, hi = min<int64_t>(P, lo + chunk);
-    float gw0 = 0.f, gw1 = 0.f, gw2 = 0.f, gb = 0.f;
-    for (int64_t p = lo; p < hi; ++p) {
-        const float* x = X + 3 * p;
-        if (layer1_pre(x, W1q, b1, j) > 0.f) {
-            const float g = dH1[p * H + j];
-            gb += g;
-            gw0 = fmaf(g, x[0], gw0);
-            gw1 = fmaf(g, x[1], gw1);
-            gw2 = fmaf(g, x[2], gw2);
+    f32x4 dw[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dw[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    float db2[2] = {0.f, 0.f}, gb[2] = {0.f, 0.f}, gw[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+    ChunkWalk it;
+    it.start(off, S, P, blockIdx.x);
+    float4 pre = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto fetch = [&]() {
+        pre = make_float4(0.f, 0.f, 0.f, 0.f);
+        const int64_t p = it.p0 + tid;
+        if (tid < 64 && it.s < S && p < it.hi) pre = make_float4(X[3 * p], X[3 * p + 1], X[3 * p + 2], a[p]);
+    };
+    auto product = [&](f32x4 (&acc)[4][2], const uint16_t* A, const uint16_t* B) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[i][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < H; k += 32) {
+            bf16x8 bf[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) bf[b] = frag16(B, H, colv[b], H, k + kq);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bf16x8 af = *reinterpret_cast<const bf16x8*>(&A[(16 * i + r16) * kTrainLd + k + kq]);
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[b], acc[i][b], 0, 0, 0);
+            }
+        }
+    };
+    fetch();
+    int buf = 0;
+    while (it.s < S) {
+        if (tid < 64) xs[buf][tid] = pre;
+        const float de[2] = {dE[it.s * H + colv[0]], dE[it.s * H + colv[1]]};
+        __syncthreads();  // also: every wavefront is done with the LDS tiles
+        it.next(off, S, P, gridDim.x);
+        fetch();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            uint32_t pk[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float h[2];
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const float4 x = xs[buf][ph + 8 * v + 2 * e + w];
+                    h[w] = fmaxf(fmaf(x.z, u2, fmaf(x.y, u1, fmaf(x.x, u0, ub))), 0.f);
+                }
+                pk[e] = pack_bf16(h[0], h[1]);
+                h1[(ph + 8 * v + 2 * e) * kTrainLd + unit] = (uint16_t)pk[e];
+                h1[(ph + 8 * v + 2 * e + 1) * kTrainLd + unit] = (uint16_t)(pk[e] >> 16);
+            }
+            *reinterpret_cast<uint4*>(&h1T[unit * kTrainLdT + ph + 8 * v]) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        }
+        __syncthreads();
+        f32x4 acc[4][2];
+        product(acc, h1, q.W2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                uint32_t pk[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    float v[2];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const int pr = 16 * i + 4 * g4 + 2 * e + w;
+                        v[w] = acc[i][b][2 * e + w] + b2v[b] > 0.f ? xs[buf][pr].w * de[b] : 0.f;
+                        db2[b] += v[w];
+                    }
+                    pk[e] = pack_bf16(v[0], v[1]);
+                    const int pr = 16 * i + 4 * g4 + 2 * e;
+                    dp[pr * kTrainLd + colv[b]] = (uint16_t)pk[e];
+                    dp[(pr + 1) * kTrainLd + colv[b]] = (uint16_t)(pk[e] >> 16);
+                }
+                *reinterpret_cast<uint2*>(&dpT[colv[b] * kTrainLdT + 16 * i + 4 * g4]) = make_uint2(pk[0], pk[1]);
+            }
+        __syncthreads();
+        product(acc, dp, q.W2T);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float4 x = xs[buf][16 * i + 4 * g4 + r];
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const float hp = fmaf(x.z, w1c[b][2], fmaf(x.y, w1c[b][1], fmaf(x.x, w1c[b][0], w1c[b][3])));
+                    const float g = hp > 0.f ? acc[i][b][r] : 0.f;
+                    gb[b] += g;
+                    gw[b][0] = fmaf(g, x.x, gw[b][0]);
+                    gw[b][1] = fmaf(g, x.y, gw[b][1]);
+                    gw[b][2] = fmaf(g, x.z, gw[b][2]);
+                }
+            }
+#pragma unroll
+        for (int k = 0; k < 64; k += 32) {
+            bf16x8 af[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                af[i] = *reinterpret_cast<const bf16x8*>(&dpT[(64 * (wave >> 1) + 16 * i + r16) * kTrainLdT + k + kq]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bf16x8 bf =
+                    *reinterpret_cast<const bf16x8*>(&h1T[(128 * (wave & 1) + 16 * j + r16) * kTrainLdT + k + kq]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    dw[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf, dw[i][j], 0, 0, 0);
+            }
+        }
+        buf ^= 1;
+    }
+    float* out = part + (int64_t)blockIdx.x * kTrainPart;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                out[(64 * (wave >> 1) + 16 * i + 4 * g4 + r) * H + 128 * (wave & 1) + 16 * j + r16] = dw[i][j][r];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        float s[5] = {gw[b][0], gw[b][1], gw[b][2], gb[b], db2[b]};
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            s[k] += __shfl_xor(s[k], 16);
+            s[k] += __shfl_xor(s[k], 32);
+        }
+        if (lane < 16) {
+            float* o = out + H * H;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) o[3 * colv[b] + k] = s[k];
+            o[3 * H + colv[b]] = s[3];
+            o[4 * H + colv[b]] = s[4];
         }
     }
-    float* o = part + (int64_t)blockIdx.x * 4 * H;
-    o[3 * j] = gw0;
-    o[3 * j + 1] = gw1;
-    o[3 * j + 2] = gw2;
-    o[3 * H + j] = gb;
+}
+
+// Gradient of the point layers from the n partials: 64 outputs per workgroup,
+// four slices of the partials each, the slices added in order.
+__global__ __launch_bounds__(256) void train_reduce_kernel(const float* __restrict__ part, int n,
+                                                           float* __restrict__ grad) {
+    __shared__ float sl[4][64];
+    const int c = threadIdx.x & 63, z = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + c;
+    float s = 0.f;
+#pragma unroll 8
+    for (int k = z * n / 4; k < (z + 1) * n / 4; ++k) s += part[(int64_t)k * kTrainPart + e];
+    sl[z][c] = s;
+    __syncthreads();
+    if (z == 0) {
+        const float t = (sl[0][c] + sl[1][c]) + (sl[2][c] + sl[3][c]);
+        const int l = e - H * H;
+        if (l < 0)
+            grad[kSgW2 + e] = t;
+        else if (l < 4 * H)
+            grad[l < 3 * H ? kSgW1 + l : kSgB1 + l - 3 * H] = t;
+        else
+            grad[kSgB2 + l - 4 * H] = t;
+    }
 }
 
 // Scatter of the head column sums into the flat gradient.
@@ -667,14 +827,6 @@ __global__ void head_grad_scatter_kernel(const float* __restrict__ hsum, const i
         grad[kSgB4] = hsum[2 * H];
         if (loss) *loss = *bad ? NAN : hsum[2 * H + 1];
     }
-}
-
-__global__ void layer1_grad_scatter_kernel(const float* __restrict__ s, float* __restrict__ grad) {
-    const int j = threadIdx.x;
-    grad[kSgW1 + 3 * j] = s[3 * j];
-    grad[kSgW1 + 3 * j + 1] = s[3 * j + 1];
-    grad[kSgW1 + 3 * j + 2] = s[3 * j + 2];
-    grad[kSgB1 + j] = s[3 * H + j];
 }
 
 // Adam with host-rounded coefficients (beta, 1 - beta each rounded once).
@@ -1058,12 +1210,16 @@ int launch_prepare(const float* theta, const SgQuant& q, void* stream) {
 }
 
 int launch_embed(const float* theta, const SgQuant& q, const float* X, const float* a, const int64_t* set_off,
-                 int64_t num_sets, int64_t num_points, float* E, void* stream) {
+                 int64_t num_sets, int64_t num_points, float* E, void* stream, bool in_order) {
     if (num_sets == 0) return 0;
     // two resident workgroups per CU (their registers), each walking its share of the sets
     const unsigned grid = (unsigned)std::min<int64_t>(num_sets, 512);
-    hipLaunchKernelGGL(embed_fused_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, a, set_off, num_sets,
-                       num_points, q, theta, E);
+    if (in_order)
+        hipLaunchKernelGGL(embed_fused_kernel<true>, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, a, set_off,
+                           num_sets, num_points, q, theta, E);
+    else
+        hipLaunchKernelGGL(embed_fused_kernel<false>, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, a, set_off,
+                           num_sets, num_points, q, theta, E);
     return (int)hipGetLastError();
 }
 
@@ -1096,17 +1252,11 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
                      void* stream) {
     hipStream_t st = (hipStream_t)stream;
     const int64_t S = 2 * B;
-    const int64_t Ppad = (P + 63) / 64 * 64;
     const int64_t Bpad = (B + 63) / 64 * 64;
     int err;
     hipLaunchKernelGGL(check_offsets_kernel, dim3(1), dim3(256), 0, st, set_off, S, P, w.bad);
-    // forward
-    hipLaunchKernelGGL(layer1_kernel, dim3(grid_for(Ppad, 1)), dim3(256), 0, st, X, P, Ppad, q.W1, theta + kSgB1,
-                       w.H1q);
-    if ((err = (int)hipGetLastError())) return err;
-    if ((err = gemm_nt(w.H1q, H, q.W2, H, w.PRE2, H, (int)P, H, H, 1, 0, st))) return err;
-    hipLaunchKernelGGL(pool_kernel, dim3((unsigned)S), dim3(256), 0, st, w.PRE2, theta + kSgB2, a, set_off, P, w.E);
-    if ((err = (int)hipGetLastError())) return err;
+    // forward: the inference kernel
+    if ((err = launch_embed(theta, q, X, a, set_off, S, P, w.E, stream, true))) return err;
     SgPredictWork pw{w.Z, w.PRE3};
     if ((err = launch_predict(theta, q, w.E, S, w.E, S, nullptr, nullptr, 1, B, pw, w.t, w.pred, stream))) return err;
     // head backward
@@ -1124,29 +1274,16 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
     if ((err = gemm_nt(w.dGq, H, q.W3T, H, w.dZ, 3 * H, (int)B, 3 * H, H, 1, 0, st))) return err;
     hipLaunchKernelGGL(dz_to_de_kernel, dim3(grid_for(B * H)), dim3(256), 0, st, w.dZ, w.E, B, w.dE);
     if ((err = (int)hipGetLastError())) return err;
-    // pooling and layer-2 backward
-    hipLaunchKernelGGL(pool_bwd_kernel, dim3((unsigned)S), dim3(256), 0, st, w.PRE2, theta + kSgB2, a, set_off, P,
-                       w.dE, w.dP2q, w.db2p);
+    // pooling and both point layers
+    const int grid = (int)std::min<int64_t>(S, kTrainGrid);
+    err = (int)hipFuncSetAttribute((const void*)train_bwd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)kTrainLds);
+    if (err) return err;
+    hipLaunchKernelGGL(train_bwd_kernel, dim3(grid), dim3(kTrainThreads), kTrainLds, st, X, a, set_off, S, P, q, theta,
+                       w.dE, w.part);
     if ((err = (int)hipGetLastError())) return err;
-    hipLaunchKernelGGL(colsum_kernel, dim3(H / 64), dim3(kColsumThreads), 0, st, w.db2p, S, (int64_t)H, H,
-                       grad + kSgB2, 0);
-    if ((err = transpose(w.dP2q, H, (int)P, (int)Ppad, H, w.dP2qT, Ppad, st))) return err;
-    if ((err = transpose(w.H1q, H, (int)P, (int)Ppad, H, w.H1qT, Ppad, st))) return err;
-    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>(64, Ppad / 2048));
-    if ((err = gemm_nt(w.dP2qT, Ppad, w.H1qT, Ppad, w.split, H, H, H, (int)Ppad, splits, (int64_t)H * H, st)))
-        return err;
-    hipLaunchKernelGGL(sum_splits_kernel, dim3(grid_for((int64_t)H * H)), dim3(256), 0, st, w.split, splits,
-                       (int64_t)H * H, grad + kSgW2, (int64_t)H * H);
-    // dH1 = dP2 W2
-    if ((err = gemm_nt(w.dP2q, H, q.W2T, H, w.dH1, H, (int)P, H, H, 1, 0, st))) return err;
-    const int64_t chunk = 512;
-    const int64_t nblk = std::max<int64_t>(1, (P + chunk - 1) / chunk);
-    hipLaunchKernelGGL(layer1_bwd_kernel, dim3((unsigned)nblk), dim3(256), 0, st, w.dH1, X, q.W1, theta + kSgB1, P,
-                       chunk, w.l1p);
-    if ((err = (int)hipGetLastError())) return err;
-    hipLaunchKernelGGL(colsum_kernel, dim3(4 * H / 64), dim3(kColsumThreads), 0, st, w.l1p, nblk, (int64_t)4 * H,
-                       4 * H, w.l1s, 0);
-    hipLaunchKernelGGL(layer1_grad_scatter_kernel, dim3(1), dim3(256), 0, st, w.l1s, grad);
+    static_assert(kTrainPart % 64 == 0, "whole workgroups");
+    hipLaunchKernelGGL(train_reduce_kernel, dim3(kTrainPart / 64), dim3(256), 0, st, w.part, grid, grad);
     return (int)hipGetLastError();
 }
 

@@ -288,3 +288,19 @@ def test_embed_chunk_edges(sizes):
     assert np.abs(E - want).max() <= 1e-3 * np.abs(want).max()
     for s, k in enumerate(sizes):
         assert k > 0 or not E[s].any()
+
+
+@pytest.mark.parametrize("pairs,sizes", [(1, [1, 65]), (2, [64, 63, 128, 1]), (130, [3, 66, 64])],
+                         ids=["one", "edges", "many-sets"])
+def test_gradient_chunk_edges(pairs, sizes):
+    """Sets that end around the 64-point chunks, fewer and more sets than
+    resident workgroups: the gradient against the twin (tolerance as in the
+    ragged-batch gradient test)."""
+    from paper_2401_07378_amd import binding
+    X, a, off = _sets(pairs, [sizes[k % len(sizes)] for k in range(2 * pairs)])
+    th = _theta(5)
+    y = W.to_f32(np.random.default_rng(pairs).uniform(0.1, 1.0, pairs))
+    loss, grad = binding.sg_loss_grad(to_dev(th), to_dev(X), to_dev(a), to_dev(off), to_dev(y))
+    wl, wg = SO.loss_and_grad(th, X, a, off, y, rounding=True)
+    assert float(loss.item()) == pytest.approx(float(wl), rel=1e-3)
+    _close_blockwise(grad.cpu().numpy(), wg, 2e-2)
