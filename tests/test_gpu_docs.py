@@ -537,3 +537,31 @@ def test_l1_documents_batched_sampled():
         gp = {"cost": float(g["costs"][p]), "stats": g["stats"][p], "src": g["src"][lo:lo + k],
               "dst": g["dst"][lo:lo + k], "flow": g["flow"][lo:lo + k]}
         assert_pair_matches(gp, ref, label=f"cand{p}")
+
+
+@pytest.mark.parametrize("d", [8, 15, 17, 300, 301])
+def test_fp32_blocked_tiles_same_as_direct(d):
+    """A launch of 256 pairs takes the blocked FP32 tiles, one pair the direct
+    form; both sum the products in k order, so every result is the same.
+    Sides around the 64-row panels, d around the 16-deep chunks."""
+    import torch
+    from paper_2401_07378_amd import binding
+    from tests.gpu_helpers import to_dev
+    r = np.random.default_rng(d)
+    ms = r.choice([1, 31, 63, 64, 65, 129], size=256)
+    ns = r.choice([1, 17, 64, 66, 128], size=256)
+    xo, yo = np.zeros(257, np.int64), np.zeros(257, np.int64)
+    xo[1:], yo[1:] = np.cumsum(ms), np.cumsum(ns)
+    X = to_dev(W.to_f32(r.standard_normal((xo[-1], d)) / np.sqrt(d)))
+    Y = to_dev(W.to_f32(r.standard_normal((yo[-1], d)) / np.sqrt(d)))
+    a = to_dev(np.concatenate([W.zipf_masses(r, int(k)) for k in ms]))
+    b = to_dev(np.concatenate([W.zipf_masses(r, int(k)) for k in ns]))
+    g = binding.emd_approx_batched(X, a, to_dev(xo), Y, b, to_dev(yo), max_m=129, max_n=128)
+    torch.cuda.synchronize()
+    cost, st = g["costs"].cpu().numpy(), binding.stats_numpy(g["stats"])
+    for p in range(0, 256, 9):
+        x0, x1, y0, y1 = xo[p], xo[p + 1], yo[p], yo[p + 1]
+        o = binding.emd_approx(X[x0:x1], a[x0:x1], Y[y0:y1], b[y0:y1], plan=False)
+        torch.cuda.synchronize()
+        s1 = binding.stats_numpy(o["stats"])[0]
+        assert float(o["cost"].item()) == cost[p] and s1.tobytes() == st[p].tobytes(), p
