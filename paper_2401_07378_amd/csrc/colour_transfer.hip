@@ -54,11 +54,12 @@ __global__ __launch_bounds__(kKmThreads) void km_init(const uint8_t* __restrict_
 // FP64 argmin or tie with it; otherwise the wavefront compares every centroid
 // in FP64 with the definition's operations, ties to the smallest index.
 // Bound: the matrix pipe (32 cycles per 256 keys).  Two 1024 x 1024 images,
-// 256 bins, 11 passes each: the whole call 2514 -> 1322 us (FP64 distances to
-// every centroid before).
+// 256 bins, 11 passes each: the whole call 2480 -> 1255 us (FP64 distances to
+// every centroid before; held to 128 registers, else the products land in
+// accumulation registers and are copied: 1322 us).
 constexpr int kKmGroups = 4;  // 64-pixel groups of a wavefront
 __host__ __device__ inline int km_pad(int K) { return (K + 15) & ~15; }
-__global__ __launch_bounds__(kKmThreads) void km_assign(const uint8_t* __restrict__ px, int64_t P, int K,
+__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(4))) void km_assign(const uint8_t* __restrict__ px, int64_t P, int K,
                                                         const double* __restrict__ C,
                                                         unsigned long long* __restrict__ S,
                                                         int32_t* __restrict__ assign) {

@@ -218,3 +218,17 @@ def test_multi_path_high_dims_ties_and_offset(d):
     Xc[5] = 1000.0
     assert_pair_matches(gpu_pair(Xc, a, Y, b, "sqeuclidean", path="multi"),
                         oracle_pair(Xc, a, Y, b, "sqeuclidean"), label=f"centre-d{d}")
+
+
+@pytest.mark.parametrize("mn", [(1, 70), (15, 1025), (17, 300), (1023, 64), (1040, 1100), (2065, 257)],
+                         ids=lambda v: "%dx%d" % v)
+@pytest.mark.parametrize("d", [1, 3, 4, 7])
+def test_search_tile_edges(mn, d):
+    """Supplier counts around the 16-record blocks and the 1024-record tiles,
+    consumer counts around the 16-consumer tiles and both block widths, every
+    record width, with exact ties (lattice) and without."""
+    m, n = mn
+    for lattice in (0, 4):
+        X, a, Y, b = W.random_pair(m + n + d, m, n, d, masses="integer" if lattice else "dirichlet", lattice=lattice)
+        g = gpu_pair(X, a, Y, b, path="multi_no_tail")
+        assert_pair_matches(g, oracle_pair(X, a, Y, b), label=f"{mn}-{d}-{lattice}")
