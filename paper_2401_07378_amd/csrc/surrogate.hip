@@ -618,7 +618,7 @@ __global__ void dz_to_de_kernel(const float* __restrict__ dZ, const float* __res
 // Before, PRE2, dP2, dH1 and two transposes went through memory (about 1.5 KB
 // a point each way) in nine launches.  Bound: matrix pipe and the W2 / W2^T
 // fragments from L2 (256 KB a chunk).  A step of 512 pairs of 256-point
-// clouds: 1783 -> 434 us.
+// clouds: 1780 -> 414 us.
 constexpr int kTrainThreads = 512;
 constexpr int kTrainGrid = 256;  // one workgroup per CU (its LDS)
 constexpr int kTrainLd = H + 8, kTrainLdT = 64 + 8;
@@ -670,17 +670,30 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[i][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        // W fragments two K steps ahead; a rolled loop (unrolled, the compiler
+        // keeps all sixteen in flight and spills)
+        bf16x8 b0[2], b1n[2];
 #pragma unroll
-        for (int k = 0; k < H; k += 32) {
-            bf16x8 bf[2];
+        for (int b = 0; b < 2; ++b) {
+            b0[b] = frag16(B, H, colv[b], H, kq);
+            b1n[b] = frag16(B, H, colv[b], H, 32 + kq);
+        }
+#pragma unroll 1
+        for (int k = 0; k < H; k += 64) {
+            const int kn = (k + 64) & (H - 1);  // the last step's read is repeated work, in bounds
 #pragma unroll
-            for (int b = 0; b < 2; ++b) bf[b] = frag16(B, H, colv[b], H, k + kq);
+            for (int hf = 0; hf < 2; ++hf) {
+                bf16x8 (&bc)[2] = hf == 0 ? b0 : b1n;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bf16x8 af = *reinterpret_cast<const bf16x8*>(&A[(16 * i + r16) * kTrainLd + k + kq]);
+                for (int i = 0; i < 4; ++i) {
+                    const bf16x8 af =
+                        *reinterpret_cast<const bf16x8*>(&A[(16 * i + r16) * kTrainLd + k + 32 * hf + kq]);
 #pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf[b], acc[i][b], 0, 0, 0);
+                    for (int b = 0; b < 2; ++b)
+                        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bc[b], acc[i][b], 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < 2; ++b) bc[b] = frag16(B, H, colv[b], H, kn + 32 * hf + kq);
             }
         }
     };
