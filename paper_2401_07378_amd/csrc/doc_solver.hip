@@ -1169,7 +1169,7 @@ __device__ void solve_doc_pair(const DocArgs& A, int64_t p, char* __restrict__ s
         if (A.protocol == NNSEMD_GREEDY)
             rank_greedy_doc<T, TIn>(L, sh, nact, kap, yn, rhat, tscale, amb, X, Y, d, A.metric, near, ties_order);
         else
-            round_rank<T>(L, nact, A.protocol, A.seed, rounds);
+            round_rank<T>(L, nact, A.seed, rounds);
         NNSEMD_PH(4)
         if constexpr (SPLIT) {
             doc_pick_distances<T>(L, kloose, nact, A.metric, kap, yn, rhat, tscale);

@@ -492,115 +492,6 @@ __global__ __launch_bounds__(kLpThreads) void lp_search(LPArgs A, int split) {
     }
 }
 
-// The same search on the matrix cores (Euclidean metrics; the keys are bit for
-// bit those of the vector form, see ps::nns_tiles): each wavefront holds
-// 4 KC tiles of 16 consumers, so one 4-byte LDS read per lane feeds 4 KC
-// blocks of 16 x 16 keys.  A block takes 32 cycles of the matrix pipe and 28
-// of the vector ALU against 75 on the vector ALU alone (d = 3).  One
-// 65536 x 65536 pair: 69.7 -> 45.8 ms for the call (held to 128 registers so
-// that the products land in vector registers: with a larger budget the compiler
-// puts them in accumulation registers and copies every one, 66.6 ms).
-template <int D, int KC>
-__global__ __launch_bounds__(kLpThreads) __attribute__((amdgpu_waves_per_eu(4))) void lp_search_mma(LPArgs A, int split) {
-    constexpr int RS = record_stride(D), KM = RS / 4, NT = 4 * KC;
-    __shared__ __align__(16) float tile[kLpTile * RS];
-    const LPState* st = A.w.st;
-    if (!lp_live(st)) return;
-    const int mact = st->mact, nact = st->nact, par = st->parity;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int base = blockIdx.x * kLpThreads * KC;
-    if (base >= nact) return;
-    const int chunk = (mact + split - 1) / split;
-    const int s_lo = min((int)blockIdx.y * chunk, mact), s_hi = min(s_lo + chunk, mact);
-    const float* __restrict__ srec = A.w.srec[par];
-    const int* __restrict__ cact = A.w.cact[par];
-    const int col = lane & 15, row = lane >> 4;
-    const int q0 = base + wave * 64 * KC;
-    float bv[NT][KM];
-    ps::Top2 best[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int q = q0 + 16 * t + col;
-        const float* yp = A.Y + (int64_t)cact[q < nact ? q : 0] * D;
-#pragma unroll
-        for (int h = 0; h < KM; ++h) {
-            const int comp = RS - 1 - (4 * h + row);
-            bv[t][h] = comp < D ? yp[comp < D ? comp : 0] - st->centre[comp < D ? comp : 0] : (comp == D ? 1.f : 0.f);
-        }
-        best[t] = {INFINITY, INFINITY, 0x7fffffff};
-    }
-    const bool idle = q0 >= nact;  // wavefront-uniform: only helps to stage
-    for (int t0 = s_lo; t0 < s_hi; t0 += kLpTile) {
-        const int cnt = min(kLpTile, s_hi - t0), pad = (cnt + 15) & ~15;
-        const float4* src = reinterpret_cast<const float4*>(srec + (size_t)t0 * RS);
-        float4* dst = reinterpret_cast<float4*>(tile);
-        for (int e = tid; e < pad * KM; e += kLpThreads) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);  // past the end: key +inf
-            if (e < cnt * KM)
-                v = src[e];
-            else if (e % KM == D / 4)
-                (&v.x)[D % 4] = INFINITY;
-            dst[e] = v;
-        }
-        __syncthreads();
-        if (!idle) {
-            const float* ap = tile + (size_t)col * RS + (RS - 1 - row);
-#pragma unroll 2
-            for (int s0 = 0; s0 < pad; s0 += 16) {
-                float av[KM];
-#pragma unroll
-                for (int h = 0; h < KM; ++h) av[h] = ap[(size_t)s0 * RS - 4 * h];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    ps::f32x4 k = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int h = 0; h < KM; ++h) k = __builtin_amdgcn_mfma_f32_16x16x4f32(av[h], bv[t][h], k, 0, 0, 0);
-                    const float o = best[t].b1;
-                    const float m = __builtin_amdgcn_fmed3f(o, k[0], k[1]);
-                    const float n = fminf(o, fminf(k[0], k[1]));
-                    const float p = __builtin_amdgcn_fmed3f(n, k[2], k[3]);
-                    best[t].b2 = fminf(best[t].b2, fminf(m, p));
-                    best[t].b1 = fminf(n, fminf(k[2], k[3]));
-                    best[t].code = best[t].b1 < o ? t0 + s0 + 4 * row : best[t].code;
-                }
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int g = 0; g < KC; ++g) {
-        const ps::Top2 w = ps::swap_merge<16>(ps::swap_merge<32>(best[4 * g], best[4 * g + 2]),
-                                              ps::swap_merge<32>(best[4 * g + 1], best[4 * g + 3]));
-        const int q = q0 + 64 * g + lane;
-        if (q >= nact) continue;
-        int bs = 0x7fffffff;
-        if (w.code != 0x7fffffff) {
-            // the first of the four slots that holds the best, from the global records
-            const float* yp = A.Y + (int64_t)cact[q] * D;
-            float y[D];
-#pragma unroll
-            for (int t = 0; t < D; ++t) y[t] = yp[t] - st->centre[t];
-            bs = w.code;
-#pragma unroll
-            for (int v = 3; v >= 0; --v) {
-                const int s = min(w.code + v, s_hi - 1);
-                float rv[RS];
-                const float4* p = reinterpret_cast<const float4*>(srec + (size_t)s * RS);
-#pragma unroll
-                for (int e = 0; e < KM; ++e) {
-                    const float4 x = p[e];
-                    rv[4 * e] = x.x;
-                    rv[4 * e + 1] = x.y;
-                    rv[4 * e + 2] = x.z;
-                    rv[4 * e + 3] = x.w;
-                }
-                bs = lp_key<D, RS, false>(rv, y) == w.b1 ? s : bs;
-            }
-        }
-        A.w.part[(size_t)blockIdx.y * A.w.ncap + q] = make_float4(w.b1, w.b2, __int_as_float(bs), 0.f);
-    }
-}
-
 
 // ---------------------------------------------------------------- decide
 // Best / second-best merge of two FP32 partials; equal keys keep the smaller
@@ -1489,10 +1380,10 @@ int lp_launch_round(const LPArgs& A, int d, int mact_ub, int nact_ub, void* stre
     NNSEMD_LP_DISPATCH(d, {
         if (kc == 4) {
             if (l1) hipLaunchKernelGGL((lp_search<DD, true, 4>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
-            else hipLaunchKernelGGL((lp_search_mma<DD, 4>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
+            else hipLaunchKernelGGL((lp_search<DD, false, 4>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
         } else {
             if (l1) hipLaunchKernelGGL((lp_search<DD, true, 1>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
-            else hipLaunchKernelGGL((lp_search_mma<DD, 1>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
+            else hipLaunchKernelGGL((lp_search<DD, false, 1>), dim3(cblocks, split), dim3(kLpThreads), 0, st, A, split);
         }
         if (l1) {
             hipLaunchKernelGGL((lp_decide<DD, true>), dim3(dblocks), dim3(kLpThreads), 0, st, A, split);

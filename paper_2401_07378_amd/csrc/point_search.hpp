@@ -341,15 +341,17 @@ __device__ inline Top2 swap_merge(Top2 x, Top2 y) {
 // the four 16-lane rows exchange tiles (lane_swap) while merging, which leaves
 // lane l with consumer l of the 64, and the four records of the winning
 // (block, row) are read once more for the first slot that holds the best.
-// Bound: a block takes 32 cycles of the matrix pipe (one tile, d <= 3) against
-// 28 of the vector ALU, where the vector form needs 75 (d = 3); what is left of
+// Bound: a block takes 32 cycles of the FP32 matrix pipe (one tile, d <= 3) and
+// 28 of vector issue, which overlap little, where the vector form needs 75
+// (d = 3; the grid-wide search of one large pair, which issues nothing else,
+// gained nothing from it and stays on the vector form); what is left of
 // the search in a launch is the latency of its first and last reads.  With the
 // coordinates in the records (no supplier row read from memory for the exact
 // key): 4096 pairs of 128..1024 points 1159 -> 1083 us, 2048 pixel grids
 // 3272 -> 2950 us, one 256 x 256 pair 52 -> 49 us (bucket-major rounds on both
 // sides).
 template <int D, int RS, int KT, typename LT>
-__device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __restrict__ Y, const float (&centre)[D], float rhat, int mact, int nact, int q0, bool exact,
+__device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __restrict__ Y, const float (&centre)[D], float rhat, int mact, int qend, int q0, bool exact,
                                  int metric) {
     const int lane = threadIdx.x & (kWave - 1);
     const int col = lane & 15, row = lane >> 4;
@@ -367,7 +369,7 @@ __device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __res
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
         const int q = q0 + 16 * t + col;
-        const float* yp = Y + (size_t)L.cact[q < nact ? q : 0] * D;
+        const float* yp = Y + (size_t)L.cact[q < qend ? q : 0] * D;
 #pragma unroll
         for (int h = 0; h < KM; ++h) {
             const int comp = RS - 1 - (4 * h + row);
@@ -377,7 +379,7 @@ __device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __res
     }
     // lane l finishes consumer q0 + l
     const int q = q0 + lane;
-    const bool valid = lane < 16 * KT && q < nact;
+    const bool valid = lane < 16 * KT && q < qend;
     const int j = L.cact[valid ? q : 0];
     float yr[D];
 #pragma unroll
@@ -502,14 +504,13 @@ __device__ inline int search_round(const LT& L, SharedCore& sh, const float* __r
         const int lo = wave * nt / NW, hi = (wave + 1) * nt / NW;
         for (int t0 = lo; t0 < hi; t0 += 4) {
             const int k = hi - t0;  // wavefront-uniform
-            if (k >= 4)
-                nns_tiles<D, RS, 4>(L, sh, Y, centre, rhat, mact, nact, 16 * t0, exact, metric);
-            else if (k == 3)
-                nns_tiles<D, RS, 3>(L, sh, Y, centre, rhat, mact, nact, 16 * t0, exact, metric);
+            const int qend = min(nact, 16 * hi);  // three tiles run as four, the last one idle
+            if (k >= 3)
+                nns_tiles<D, RS, 4>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
             else if (k == 2)
-                nns_tiles<D, RS, 2>(L, sh, Y, centre, rhat, mact, nact, 16 * t0, exact, metric);
+                nns_tiles<D, RS, 2>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
             else
-                nns_tiles<D, RS, 1>(L, sh, Y, centre, rhat, mact, nact, 16 * t0, exact, metric);
+                nns_tiles<D, RS, 1>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
         }
     } else if (S > 1) {
         nns_pass<D, RS, L1, 1, UN>(L, sh, Y, centre, rhat, mact, nact, S, tid / S, T / S, tid & (S - 1), exact, metric);

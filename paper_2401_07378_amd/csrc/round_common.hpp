@@ -4,10 +4,12 @@
 // after the search has stored every active consumer's pick (active supplier
 // slot in cnn[j], exact FP64 key in ckey[j]) and counted it into scnt[slot]:
 //   round_buckets  claimant sets a_i: scan of the counts, scatter
-//   round_rank     each claimant's place in its bucket: (D_ij, j) order for
-//                  the greedy protocol, (random key, j) for the random one
+//   round_rank     each claimant's place in its bucket
 //   round_walk     one lane per claimed supplier serves in that order (FP64)
 //   round_compact  plan append + surviving suppliers / consumers
+// in two forms: consumer-major (document path, whose greedy order works on
+// FP32 keys with exact ones filled in where needed) and bucket-major (*_pos:
+// point path, given-D path, single-workgroup finish).
 // Every function ends with a workgroup barrier; all of them must be called
 // by every thread of the workgroup with block-uniform arguments.
 #pragma once
@@ -296,73 +298,27 @@ __device__ inline void round_buckets(const LT& L, SharedCore& sh, int mact, int 
     __syncthreads();
 }
 
-// ---- claimant order: each claimant counts the bucket members that precede
-// it and writes itself to that rank; no dependent chains.  When the serve
-// order shares the buckets' storage (compact layout), every rank is taken
-// first (at most CS claimants per thread, kept in registers) and written
-// after a barrier.  With `ties_order` (greedy order, exact FP64 keys) the
-// same scan keeps the largest key below the claimant's -- its neighbour's
-// in the serve order over the whole bucket -- and counts the pair when the
-// two distances are a near tie.
-template <typename LT>
-__device__ inline int claimant_place(const LT& L, int j, int protocol, uint64_t seed, int rounds, int metric,
-                                     unsigned long long* ties_order) {
-    const int sl = L.cnn[j];
-    const int c = L.scnt[sl];
-    const int end = L.soff[sl];
-    const int start = end - c;
-    int rank = 0;
-    if (c > 1) {
-        if (protocol == NNSEMD_GREEDY) {
-            const double k = L.ckey[j];
-            double pk = -1.0;  // keys are >= +0: -1 = no predecessor
+// ---- claimant order of the random protocol: each claimant counts the bucket
+// members with a smaller (random key, j) and writes itself to that rank in the
+// separate serve-order array.
+template <int T, typename LT>
+__device__ inline void round_rank(const LT& L, int nact, uint64_t seed, int rounds) {
+    for (int q = threadIdx.x; q < nact; q += T) {
+        const int j = L.cact[q];
+        const int sl = L.cnn[j];
+        const int c = L.scnt[sl];
+        const int end = L.soff[sl];
+        int rank = 0;
+        if (c > 1) {
+            const uint64_t k = rp_key(seed, rounds, j);
 #pragma unroll 4
-            for (int e = start; e < end; ++e) {
+            for (int e = end - c; e < end; ++e) {
                 const int j2 = L.list[e];
-                const double k2 = L.ckey[j2];
-                const bool below = (k2 < k) || (k2 == k && j2 < j);
-                rank += below;
-                if (below && k2 > pk) pk = k2;
-            }
-            if (ties_order != nullptr && pk >= 0.0 && keys_near(pk, k, metric)) atomicAdd(ties_order, 1ull);
-        } else {
-            // the random order is drawn for the caller's consumer indices
-            const uint64_t k = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j] : j);
-#pragma unroll 4
-            for (int e = start; e < end; ++e) {
-                const int j2 = L.list[e];
-                const uint64_t k2 = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j2] : j2);
+                const uint64_t k2 = rp_key(seed, rounds, j2);
                 rank += (k2 < k) || (k2 == k && j2 < j);
             }
         }
-    }
-    return start + rank;
-}
-
-template <int T, int CS = 1, typename LT>
-__device__ inline void round_rank(const LT& L, int nact, int protocol, uint64_t seed, int rounds, int metric = 0,
-                                  unsigned long long* ties_order = nullptr) {
-    if (L.sorted == L.list) {
-        int pos[CS], jv[CS];
-#pragma unroll
-        for (int u = 0; u < CS; ++u) {
-            const int q = threadIdx.x + u * T;
-            pos[u] = -1;
-            jv[u] = 0;
-            if (q < nact) {
-                jv[u] = L.cact[q];
-                pos[u] = claimant_place(L, jv[u], protocol, seed, rounds, metric, ties_order);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < CS; ++u)
-            if (pos[u] >= 0) L.sorted[pos[u]] = jv[u];
-    } else {
-        for (int q = threadIdx.x; q < nact; q += T) {
-            const int j = L.cact[q];
-            L.sorted[claimant_place(L, j, protocol, seed, rounds, metric, ties_order)] = j;
-        }
+        L.sorted[end - c + rank] = j;
     }
     __syncthreads();
 }
@@ -370,13 +326,10 @@ __device__ inline void round_rank(const LT& L, int nact, int protocol, uint64_t 
 // ---- flow & cost: one lane per claimed supplier walks its ordered
 // claimants while it still holds mass.  A served claimant records the local
 // index of its supplier (for the plan) and its flow in place of its key; an
-// unserved one gets flow 0.  With NEGF (every key is >= +0 when the walk
-// starts) the flow is stored negated and unserved claimants keep their keys,
-// so the walk never visits the unserved part of a bucket (one serve can
-// exhaust a supplier with thousands of claimants); round_compact must then be
-// told the same.  With COST (the keys are the exact FP64 keys), `cost`
-// accumulates this thread's part of R; without it, R is left to the caller.
-template <int T, bool COST = true, bool NEGF = false, typename LT>
+// unserved one gets flow 0.  With COST (the keys are the exact FP64 keys),
+// `cost` accumulates this thread's part of R; without it, R is left to the
+// caller.
+template <int T, bool COST = true, typename LT>
 __device__ inline void round_walk(const LT& L, int mact, int metric, double& cost) {
     for (int s = threadIdx.x; s < mact; s += T) {
         const int c = L.scnt[s];
@@ -393,12 +346,11 @@ __device__ inline void round_walk(const LT& L, int mact, int metric, double& cos
             sm = sm - f;
             L.cmass[j] = cm - f;
             if constexpr (COST) cost = cost + f * dist_of_key(L.ckey[j], metric);
-            L.ckey[j] = NEGF ? -f : f;
+            L.ckey[j] = f;
             L.cnn[j] = isup;
             ++pos;
         }
-        if constexpr (!NEGF)
-            for (int e = pos; e < end; ++e) L.ckey[L.sorted[e]] = 0.0;
+        for (int e = pos; e < end; ++e) L.ckey[L.sorted[e]] = 0.0;
         L.smass[s] = sm;
     }
     __syncthreads();
@@ -406,7 +358,7 @@ __device__ inline void round_walk(const LT& L, int mact, int metric, double& cos
 
 // ---- weights update: plan append + compaction of the active sets (and of
 // the RS-float search records when RS > 0), one scan for all three streams.
-template <int T, int CSMAX, int RS, bool NEGF = false, typename LT>
+template <int T, int CSMAX, int RS, typename LT>
 __device__ inline void round_compact(const LT& L, SharedCore& sh, int& mact, int& nact, int64_t& nnz,
                                      int32_t* plan_src, int32_t* plan_dst, double* plan_flow, int64_t plan_base) {
     constexpr int RSA = RS > 0 ? RS : 4;
@@ -426,11 +378,10 @@ __device__ inline void round_compact(const LT& L, SharedCore& sh, int& mact, int
             const int k = plo + u;
             pj[u] = k < phi ? (int)L.sorted[k] : 0;
             pf[u] = k < phi ? L.ckey[pj[u]] : 0.0;
-            if constexpr (NEGF) pf[u] = pf[u] < 0.0 ? -pf[u] : 0.0;
             kp += pf[u] > 0.0;
         }
     } else {
-        for (int k = plo; k < phi; ++k) kp += NEGF ? L.ckey[L.sorted[k]] < 0.0 : L.ckey[L.sorted[k]] > 0.0;
+        for (int k = plo; k < phi; ++k) kp += L.ckey[L.sorted[k]] > 0.0;
     }
     const int cs = (mact + T - 1) / T;
     const int slo = min(tid * cs, mact);
@@ -482,7 +433,7 @@ __device__ inline void round_compact(const LT& L, SharedCore& sh, int& mact, int
         } else {
             for (int k = plo; k < phi; ++k) {
                 const int j = L.sorted[k];
-                const double f = NEGF ? -L.ckey[j] : L.ckey[j];
+                const double f = L.ckey[j];
                 if (f > 0.0) {
                     const int64_t e = plan_base + nnz + wp;
                     plan_src[e] = L.cnn[j];

@@ -224,9 +224,9 @@ def test_multi_path_high_dims_ties_and_offset(d):
                          ids=lambda v: "%dx%d" % v)
 @pytest.mark.parametrize("d", [1, 3, 4, 7])
 def test_search_tile_edges(mn, d):
-    """Supplier counts around the 16-record blocks and the 1024-record tiles,
-    consumer counts around the 16-consumer tiles and both block widths, every
-    record width, with exact ties (lattice) and without."""
+    """Supplier counts around the record blocks and the 1024-record tiles,
+    consumer counts around both block widths, every record width, with exact
+    ties (lattice) and without."""
     m, n = mn
     for lattice in (0, 4):
         X, a, Y, b = W.random_pair(m + n + d, m, n, d, masses="integer" if lattice else "dirichlet", lattice=lattice)
