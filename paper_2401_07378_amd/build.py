@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libnnsemd.so")
-SOURCES = ["api.hip", "pair_solver.hip", "large_pair.hip", "doc_solver.hip", "surrogate.hip",
+SOURCES = ["pair_solver.hip", "pair_solver_coords.hip", "api.hip", "large_pair.hip", "doc_solver.hip", "surrogate.hip",
            "transport_map.hip", "cost_solver.hip", "colour_transfer.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -29,6 +29,8 @@ def _stale(src: str, obj: str) -> bool:
     if not os.path.exists(obj):
         return True
     deps = [os.path.join(CSRC, src)] + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hpp")]
+    if src == "pair_solver_coords.hip":
+        deps.append(os.path.join(CSRC, "pair_solver.hip"))
     deps.append(os.path.join(INCLUDE, "nnsemd.h"))
     return max(os.path.getmtime(p) for p in deps) > os.path.getmtime(obj)
 

@@ -305,6 +305,7 @@ void pair_solver_kernel(PairSolverArgs A) {
     solve_pair<D, T, CSMAX, L1, CL>(A, p, L, sh);
 }
 
+#ifndef NNSEMD_PAIR_COORDS_TU
 // Longest-first schedule: order[] lists the pairs by decreasing m * n (in
 // quarter-octave buckets; order inside a bucket is arbitrary and does not
 // affect any result), so the largest pairs start first and the short ones
@@ -349,6 +350,7 @@ __global__ __launch_bounds__(1024) void order_kernel(const int64_t* __restrict__
         order[pos] = (int32_t)p;
     }
 }
+#endif  // NNSEMD_PAIR_COORDS_TU
 
 template <int D, int T, int CSMAX, bool L1, bool CL>
 int launch_typed(const PairSolverArgs& A, size_t lds, int grid, hipStream_t st) {
@@ -413,9 +415,28 @@ int dispatch_cl(bool run, const PairSolverArgs& A, int d, int threads, int chunk
     return (int)hipErrorInvalidValue;
 }
 
+}  // namespace
+
+// The variants with coordinates in LDS are compiled as a translation unit of
+// their own (pair_solver_coords.hip includes this file), beside the others:
+// together they take the compiler twice as long.
+int dispatch_pair_coords(bool run, const PairSolverArgs& A, int d, int threads, int chunk_max, size_t lds, int grid,
+                         void* stream, int* blocks);
+
+#ifdef NNSEMD_PAIR_COORDS_TU
+
+int dispatch_pair_coords(bool run, const PairSolverArgs& A, int d, int threads, int chunk_max, size_t lds, int grid,
+                         void* stream, int* blocks) {
+    return dispatch_cl<true>(run, A, d, threads, chunk_max, lds, grid, (hipStream_t)stream, blocks);
+}
+
+#else
+
+namespace {
+
 int dispatch_all(bool run, const PairSolverArgs& A, int d, int threads, int chunk_max, size_t lds,
                  int grid, hipStream_t st, int* blocks, bool coords) {
-    return coords ? dispatch_cl<true>(run, A, d, threads, chunk_max, lds, grid, st, blocks)
+    return coords ? dispatch_pair_coords(run, A, d, threads, chunk_max, lds, grid, (void*)st, blocks)
                   : dispatch_cl<false>(run, A, d, threads, chunk_max, lds, grid, st, blocks);
 }
 
@@ -440,5 +461,6 @@ int pair_solver_blocks_per_cu(int d, int metric, int threads, int chunk_max, siz
     return dispatch_all(false, A, d, threads, chunk_max, lds_bytes, 0, nullptr, blocks, coords);
 }
 
+#endif  // NNSEMD_PAIR_COORDS_TU
 
 }  // namespace nnsemd
