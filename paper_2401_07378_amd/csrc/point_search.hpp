@@ -80,9 +80,14 @@ __device__ inline int frac_bits(float v) {
 
 // The same of a centred coordinate xc = fl(x - c), which only counts when the
 // subtraction did not round (a point near zero can lose its low bits to a
-// larger centre and then look like a lattice point).
+// larger centre and then look like a lattice point).  x - c can need more bits
+// than FP64 has, too (x = 1, c = 2^-53), so the FP64 difference is taken with
+// its rounding error (Knuth's two-sum) and has to be free of one.
 __device__ inline int centred_bits(float x, float c, float xc) {
-    return (double)xc + (double)c == (double)x ? frac_bits(xc) : 200;
+    const double xd = (double)x, cd = (double)c;
+    const double s = xd - cd, t = s - xd;
+    const double err = (xd - (s - t)) - (cd + t);
+    return s == (double)xc && err == 0.0 ? frac_bits(xc) : 200;
 }
 
 // Exact-key test.  If every centred coordinate is a multiple of 2^-q with

@@ -53,6 +53,23 @@ def test_centre_that_hides_low_bits():
     assert_pair_matches(g, oracle_pair(X, a, Y, a, "l2"), label="l2")
 
 
+@pytest.mark.parametrize("protocol", ["greedy", "random"])
+@pytest.mark.parametrize("y", [1.0, 2.0, -1.0])
+@pytest.mark.parametrize("d", [1, 3])
+def test_centre_below_the_coordinates_last_fp64_bit(d, y, protocol):
+    """Two coincident suppliers at +-2^-53 (so that is the centre) and six
+    consumers at y: y - c needs more bits than FP64 has, so the pair must not
+    pass for a lattice.  The keys have all 53 bits; equal ones are served by
+    consumer index."""
+    X = np.full((2, d), np.sign(y) * 2.0 ** -53, np.float32)
+    Y = np.full((6, d), y, np.float32)
+    a = np.full(2, 0.5, np.float32)
+    b = np.array([0.25, 0.125, 0.25, 0.125, 0.125, 0.125], np.float32)
+    for metric in ("l2", "sqeuclidean"):
+        g = gpu_pair(X, a, Y, b, metric, protocol=protocol, seed=9)
+        assert_pair_matches(g, oracle_pair(X, a, Y, b, metric, protocol=protocol, seed=9), label=f"{metric}-{y}")
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("mn", [(1, 400), (257, 255), (513, 1024), (1500, 1300)], ids=lambda v: "%dx%d" % v)
 def test_given_d_ties(mn, dtype):
