@@ -339,7 +339,9 @@ __device__ inline Top2 swap_merge(Top2 x, Top2 y) {
 // products to the accumulator one after the other, each a fused multiply-add
 // rounded to nearest (checked on gfx950 against fmaf, bit for bit, with
 // subnormals), so with the record's components fed last to first the keys are
-// exactly key32's: nothing downstream can tell the two searches apart.
+// exactly key32's: nothing downstream can tell the two searches apart.  (The
+// slot of the best is found by that equality; a key that no record gives again
+// would send its consumer to the FP64 re-score.)
 // Lane l holds the keys of suppliers 4 (l / 16) + 0..3 of a block against
 // consumer l % 16; four keys update (best, second) with two med3 and three
 // min3 and the block is remembered when the best falls strictly.  At the end
@@ -453,11 +455,12 @@ __device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __res
         yn2 = fmaf(yc, yc, yn2);
         y[k] = -2.f * yc;
     }
-    const bool flag = settle<D, false>(sh, w.b1, w.b2, yn2, rhat, valid && mact > 1, exact, metric);
-    // the first of the four slots that holds the best (a flagged consumer's
-    // pick is open: any slot will do)
+    bool flag = settle<D, false>(sh, w.b1, w.b2, yn2, rhat, valid && mact > 1, exact, metric);
+    // the first of the four slots that holds the best; should none of them give
+    // the best again, the pick is not known and the consumer is flagged (exact
+    // keys, whose near ties are counted by now, are the same in any form)
     const int c0 = min(w.code, mact - 1);
-    int pick = c0;
+    int pick = -1;
     float px[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) px[k] = 0.f;
@@ -471,6 +474,7 @@ __device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __res
 #pragma unroll
         for (int k = 0; k < D; ++k) px[k] = take ? rv[k] : px[k];
     }
+    flag |= pick < 0;
     if (valid) store_pick<D, false>(L, sh, px, yr, j, flag, pick);
 }
 

@@ -70,6 +70,33 @@ def test_centre_below_the_coordinates_last_fp64_bit(d, y, protocol):
         assert_pair_matches(g, oracle_pair(X, a, Y, b, metric, protocol=protocol, seed=9), label=f"{metric}-{y}")
 
 
+@pytest.mark.parametrize("kind", ["unit", "mixed", "tiny", "large"])
+@pytest.mark.parametrize("d", [1, 3, 4, 7])
+def test_matrix_core_keys_are_the_vector_keys(d, kind):
+    """The matrix-core search (64 consumers and more) finds its slot by the
+    equality of its keys with the fused multiply-add chain's; a key without an
+    equal is re-scored.  One round of 128 consumers must therefore re-score as
+    many as the vector search of the same consumers in four calls of 32, also
+    where products and norms are subnormal or span many binades."""
+    rng = np.random.default_rng(40 + d)
+    m, n = 301, 128
+
+    def points(k):
+        p = rng.uniform(-1, 1, size=(k, d))
+        if kind == "mixed":
+            p *= 10.0 ** rng.uniform(-22, 0, size=(k, d))
+        return W.to_f32(p * {"tiny": 1e-20, "large": 1e15}.get(kind, 1.0))
+
+    X, Y = points(m), points(n)
+    a, b = np.full(m, 1.0 / m, np.float32), np.full(n, 1.0 / n, np.float32)
+    whole = int(gpu_pair(X, a, Y, b, max_rounds=1)["stats"]["rescored"])
+    b4 = np.full(32, 1.0 / 32, np.float32)
+    parts = [int(gpu_pair(X, a, Y[k:k + 32], b4, max_rounds=1)["stats"]["rescored"]) for k in range(0, n, 32)]
+    assert whole == sum(parts)
+    assert whole < n or kind in ("tiny", "mixed")
+    assert_pair_matches(gpu_pair(X, a, Y, b), oracle_pair(X, a, Y, b), label=kind)
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("mn", [(1, 400), (257, 255), (513, 1024), (1500, 1300)], ids=lambda v: "%dx%d" % v)
 def test_given_d_ties(mn, dtype):
