@@ -1005,6 +1005,7 @@ nnsemd_status_t nnsemd_colour_transfer(nnsemd_handle_t h, const uint8_t* ref_rgb
     const int64_t cap = (int64_t)k_ref + k_src - 1;
     const size_t opf = c.take(8 * (size_t)cap), ops = c.take(4 * (size_t)cap), opd = c.take(4 * (size_t)cap);
     const size_t ost = c.take(sizeof(nnsemd_stats_t)), ocost = c.take(8), omap = c.take(24 * (size_t)k_src);
+    const size_t orec = c.take(kmeans_record_bytes(std::max(k_ref, k_src)));  // one clustering after the other
     if ((s = grow(h, &h->ct_ws, &h->ct_bytes, align_up(c.off, 256), "colour transfer workspace")) != NNSEMD_OK)
         return s;
     char* b = h->ct_ws;
@@ -1024,8 +1025,9 @@ nnsemd_status_t nnsemd_colour_transfer(nnsemd_handle_t h, const uint8_t* ref_rgb
     nnsemd_stats_t* st = stats ? stats : reinterpret_cast<nnsemd_stats_t*>(b + ost);
     double* cst = cost ? cost : reinterpret_cast<double*>(b + ocost);
     double* T = reinterpret_cast<double*>(b + omap);
-    int err = launch_kmeans(ref_rgb, ref_pixels, k_ref, iters, Cr, Sr, Ar, Xr, ar, stream);
-    if (err == 0) err = launch_kmeans(src_rgb, src_pixels, k_src, iters, Cs, Ss, As, Ys, bs, stream);
+    float* rec = reinterpret_cast<float*>(b + orec);
+    int err = launch_kmeans(ref_rgb, ref_pixels, k_ref, iters, Cr, Sr, rec, Ar, Xr, ar, stream);
+    if (err == 0) err = launch_kmeans(src_rgb, src_pixels, k_src, iters, Cs, Ss, rec, As, Ys, bs, stream);
     if (err != 0) return device_fail(h, err, "palette reduction");
     nnsemd_options_t oc = o;
     oc.path = NNSEMD_PATH_ON_CHIP;

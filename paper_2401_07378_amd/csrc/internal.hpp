@@ -365,10 +365,12 @@ int launch_barycentric_map(const int32_t* src, const int32_t* dst, const double*
 // ---------------------------------------------------------------------
 // Colour transfer application (colour_transfer.hip).
 size_t kmeans_lds_bytes(int K);
+size_t kmeans_record_bytes(int K);
 // K-means palette of P 8-bit RGB pixels (iters update steps, then the final
-// assignment): centroids C (K x 3, FP64), sums/counts S (K x 4), assignment,
-// palette points (K x 3 FP32) and masses (K FP32).
-int launch_kmeans(const uint8_t* px, int64_t P, int K, int iters, double* C, unsigned long long* S,
+// assignment): centroids C (K x 3, FP64), sums/counts S (K x 4), search records
+// (kmeans_record_bytes, 16-byte aligned), assignment, palette points (K x 3
+// FP32) and masses (K FP32).
+int launch_kmeans(const uint8_t* px, int64_t P, int K, int iters, double* C, unsigned long long* S, float* records,
                   int32_t* assign, float* pts, float* mass, void* stream);
 int launch_recolour(const uint8_t* px, const int32_t* assign, int64_t P, const double* T, uint8_t* out,
                     void* stream);

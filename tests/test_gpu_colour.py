@@ -73,3 +73,29 @@ def test_palette_edges(pixels, k, levels):
     for f in ("ref_palette", "ref_mass", "src_palette", "src_mass", "assign"):
         np.testing.assert_array_equal(g[f], want[f])
     np.testing.assert_array_equal(g["image"].reshape(-1, 3), want["image"])
+
+
+@pytest.mark.parametrize("k", [1, 16, 63, 64, 65, 256, 1000])
+@pytest.mark.parametrize("pixels", [1500, 130816, 130817, 270001])
+@pytest.mark.parametrize("kind", ["flat", "few"])
+def test_palette_repeated_colours(kind, pixels, k):
+    """Images whose starting centroids repeat (three quarters white; four
+    levels a channel): equal centroids leave the scan, many pixels of one
+    wavefront are settled in FP64 together.  Pixel counts around the line
+    between the direct and the scanning form (512 workgroups, K = 64) and with
+    two groups a wavefront."""
+    r = np.random.default_rng(k + pixels)
+    img = []
+    for _ in range(2):
+        if kind == "flat":
+            p = np.full((pixels, 3), 255, np.uint8)
+            q = pixels // 4
+            p[:q] = np.clip(120 + 60 * np.sin(np.arange(q)[:, None] / [300, 500, 700]) + r.normal(0, 2, (q, 3)), 0, 255)
+        else:
+            p = (r.integers(0, 4, size=(pixels, 3)) * 85).astype(np.uint8)
+        img.append(p)
+    g = _run(*img, k, k, 2)
+    want = oracle.colour_transfer(*img, k, k, 2, "l2")
+    for f in ("ref_palette", "ref_mass", "src_palette", "src_mass", "assign"):
+        np.testing.assert_array_equal(g[f], want[f])
+    np.testing.assert_array_equal(g["image"].reshape(-1, 3), want["image"])
