@@ -1575,7 +1575,7 @@ static size_t sg_train_carve(char* base, int64_t B, bool own_grad, sg::SgTrainWo
     const size_t oPRE3 = c.take(4 * Bpad * Hd), odZ = c.take(4 * Bpad * 3 * Hd);
     const size_t oHB = c.take(4 * Bpad * kSgHbCols), ohs = c.take(4 * kSgHbCols);
     const size_t ot = c.take(4 * Bpad), opred = c.take(4 * Bpad);
-    const size_t opart = c.take(4 * (size_t)std::min<int64_t>(S, 256) * kSgTrainPart);
+    const size_t opart = c.take(4 * (size_t)std::min<int64_t>(S, kSgTrainGrid) * kSgTrainPart);
     const size_t obad = c.take(64);
     const size_t ograd = own_grad ? c.take(4 * kSgParams) : 0;
     if (base != nullptr) {

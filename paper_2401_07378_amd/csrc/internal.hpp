@@ -259,6 +259,7 @@ constexpr int64_t kSgB4 = kSgW4 + kSgHidden;
 constexpr int64_t kSgParams = kSgB4 + 1;
 constexpr int kSgHbCols = 2 * kSgHidden + 8;  // head-backward row: dg | dt*g | dt | r^2/B | pad
 constexpr int kSgTrainPart = kSgHidden * kSgHidden + 5 * kSgHidden;  // partial gradient of the point layers
+constexpr int kSgTrainGrid = 256;  // workgroups of their backward (one per CU, its LDS), at most: one partial each
 constexpr int kSgTopkMax = 1024;
 
 namespace sg {
@@ -279,7 +280,7 @@ struct SgTrainWork {
     float *E, *dE;                        // 2B x H
     uint16_t *Z, *ZT, *dGq, *dGqT;        // Bpad x 3H, 3H x Bpad, Bpad x H, H x Bpad
     float *PRE3, *dZ, *HB, *hsum, *t, *pred;
-    float* part;                          // min(2B, 256) partial gradients of the point layers
+    float* part;                          // min(2B, kSgTrainGrid) partial gradients of the point layers
     int* bad;  // offsets check
 };
 int launch_prepare(const float* theta, const SgQuant& q, void* stream);

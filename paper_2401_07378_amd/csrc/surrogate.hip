@@ -620,7 +620,6 @@ __global__ void dz_to_de_kernel(const float* __restrict__ dZ, const float* __res
 // fragments from L2 (256 KB a chunk).  A step of 512 pairs of 256-point
 // clouds: 1780 -> 414 us.
 constexpr int kTrainThreads = 512;
-constexpr int kTrainGrid = 256;  // one workgroup per CU (its LDS)
 constexpr int kTrainLd = H + 8, kTrainLdT = 64 + 8;
 constexpr size_t kTrainLds = 2 * sizeof(uint16_t) * (64 * (size_t)kTrainLd + H * (size_t)kTrainLdT);
 // partial: dW2 (H x H), dW1 (H x 3), db1 (H), db2 (H)
@@ -1288,7 +1287,7 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
     hipLaunchKernelGGL(dz_to_de_kernel, dim3(grid_for(B * H)), dim3(256), 0, st, w.dZ, w.E, B, w.dE);
     if ((err = (int)hipGetLastError())) return err;
     // pooling and both point layers
-    const int grid = (int)std::min<int64_t>(S, kTrainGrid);
+    const int grid = (int)std::min<int64_t>(S, kSgTrainGrid);
     err = (int)hipFuncSetAttribute((const void*)train_bwd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)kTrainLds);
     if (err) return err;
