@@ -61,9 +61,9 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // compact (point path): 16-bit index arrays (even lengths, 4-byte aligned,
 // so a packed 32-bit counter atomic stays inside its array) and the FP64 key
 // array at least kPairRedBytes long: it is the block reductions' scratch
-// outside the rounds.  share (compact only): the serve order is written over
-// the claimant buckets (one more barrier per round, 2 bytes less per
-// consumer).
+// outside the rounds.  share: the serve order is written over the claimant
+// buckets (the bucket-major phases); otherwise it has an array of its own (the
+// document path).
 constexpr size_t kPairRedBytes = 8 * 17 * 8;
 __host__ __device__ inline PairLdsLayout pair_lds_layout(int M, int N, int rs, int cd = 0, bool compact = false,
                                                          bool share = true) {
@@ -84,7 +84,7 @@ __host__ __device__ inline PairLdsLayout pair_lds_layout(int M, int N, int rs, i
     L.cact = o;  o += isz * Ne;
     L.cnn = o;   o += isz * Ne;
     L.list = o;  o += isz * Ne;
-    if (compact && share) {
+    if (share) {
         L.sorted = L.list;
     } else {
         L.sorted = o; o += isz * Ne;

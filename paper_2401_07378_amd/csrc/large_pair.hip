@@ -1215,7 +1215,7 @@ constexpr int kLpTailThreads = 512;
 constexpr int kLpTailChunk = 4;  // points per thread and side: capacity 2048
 
 __host__ __device__ inline size_t lp_tail_lds(int cap, int rs) {
-    return align_up(pair_lds_layout(cap, cap, rs, 0, false, false).total, 16) + sizeof(int32_t) * (size_t)cap;
+    return align_up(pair_lds_layout(cap, cap, rs).total, 16) + sizeof(int32_t) * (size_t)cap;
 }
 
 template <int D, bool L1>
@@ -1229,7 +1229,7 @@ __global__ __launch_bounds__(kLpTailThreads) void lp_tail(LPArgs A) {
     if (!(st->status == NNSEMD_OK && !st->done && st->tail)) return;  // uniform
     const int cap = A.tail_cap;
     rc::Lds L = rc::carve(lds_dyn, cap, cap, RS);
-    int32_t* jmap = reinterpret_cast<int32_t*>(lds_dyn + align_up(pair_lds_layout(cap, cap, RS, 0, false, false).total, 16));
+    int32_t* jmap = reinterpret_cast<int32_t*>(lds_dyn + align_up(pair_lds_layout(cap, cap, RS).total, 16));
     L.jmap = jmap;
     const int tid = threadIdx.x;
     const int par = st->parity;

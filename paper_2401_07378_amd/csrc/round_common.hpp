@@ -52,7 +52,7 @@ struct LdsT {
     I* cact;        // [N] active consumers, compacted, ascending
     I* cnn;         // [N] pick (active slot) by consumer; after the serve: supplier local index
     I* list;        // [N] near-tie consumers during the search; claimant buckets after
-    I* sorted;      // [N] claimant buckets in serve order (the list's storage when compact)
+    I* sorted;      // [N] claimant buckets in serve order (the list's storage when shared)
     float* yl;      // [N * cd] consumer coordinates by local index (coordinate variant only)
     const int32_t* jmap;  // [N] caller's consumer index of each local one (null: the same)
 };

@@ -13,7 +13,7 @@
 // activations, pooling and the optimiser are FP32.
 //
 // Kernels: a generic BF16 "NT" GEMM on v_mfma_f32_16x16x32_bf16 (C = A B^T,
-// both operands K-contiguous, optional split-K), a fused phi + pooling
+// both operands K-contiguous), a fused phi + pooling
 // kernel for inference (one workgroup per set, no workspace), unfused layer
 // kernels for training, LDS transposes, deterministic column sums, Adam, and
 // a radix top-k.
@@ -90,49 +90,43 @@ __global__ void prepare_kernel(const float* __restrict__ theta, SgQuant q) {
 }
 
 // ---------------------------------------------------------------- GEMM
-// C[M x N] (+ split z * c_split) = A[M x K] B[N x K]^T over K range of split z.
+// C[M x N] = A[M x K] B[N x K]^T.
 // Workgroup tile 64 x 64, four wavefronts of 32 x 32 (2 x 2 MFMA blocks).
 // Requires lda, ldb multiples of 8, K multiple of 32, 16-byte aligned bases.
 __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                       const uint16_t* __restrict__ B, int64_t ldb,
-                                                      float* __restrict__ C, int64_t ldc, int M, int N, int K,
-                                                      int kchunk, int64_t c_split) {
+                                                      float* __restrict__ C, int64_t ldc, int M, int N, int K) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int m0 = blockIdx.x * 64 + (wave >> 1) * 32;
     const int n0 = blockIdx.y * 64 + (wave & 1) * 32;
-    const int kb = blockIdx.z * kchunk;
-    const int ke = min(K, kb + kchunk);
     const int r16 = lane & 15, kq = 8 * (lane >> 4);
     f32x4 acc[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    if (kb < ke) {
-        bf16x8 a0 = frag16(A, lda, m0 + r16, M, kb + kq);
-        bf16x8 a1 = frag16(A, lda, m0 + 16 + r16, M, kb + kq);
-        bf16x8 b0 = frag16(B, ldb, n0 + r16, N, kb + kq);
-        bf16x8 b1 = frag16(B, ldb, n0 + 16 + r16, N, kb + kq);
-        for (int k = kb; k < ke; k += 32) {
-            bf16x8 na0 = a0, na1 = a1, nb0 = b0, nb1 = b1;
-            if (k + 32 < ke) {
-                na0 = frag16(A, lda, m0 + r16, M, k + 32 + kq);
-                na1 = frag16(A, lda, m0 + 16 + r16, M, k + 32 + kq);
-                nb0 = frag16(B, ldb, n0 + r16, N, k + 32 + kq);
-                nb1 = frag16(B, ldb, n0 + 16 + r16, N, k + 32 + kq);
-            }
-            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc[1][1], 0, 0, 0);
-            a0 = na0;
-            a1 = na1;
-            b0 = nb0;
-            b1 = nb1;
+    bf16x8 a0 = frag16(A, lda, m0 + r16, M, kq);
+    bf16x8 a1 = frag16(A, lda, m0 + 16 + r16, M, kq);
+    bf16x8 b0 = frag16(B, ldb, n0 + r16, N, kq);
+    bf16x8 b1 = frag16(B, ldb, n0 + 16 + r16, N, kq);
+    for (int k = 0; k < K; k += 32) {
+        bf16x8 na0 = a0, na1 = a1, nb0 = b0, nb1 = b1;
+        if (k + 32 < K) {
+            na0 = frag16(A, lda, m0 + r16, M, k + 32 + kq);
+            na1 = frag16(A, lda, m0 + 16 + r16, M, k + 32 + kq);
+            nb0 = frag16(B, ldb, n0 + r16, N, k + 32 + kq);
+            nb1 = frag16(B, ldb, n0 + 16 + r16, N, k + 32 + kq);
         }
+        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc[0][0], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b1, acc[0][1], 0, 0, 0);
+        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc[1][0], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc[1][1], 0, 0, 0);
+        a0 = na0;
+        a1 = na1;
+        b0 = nb0;
+        b1 = nb1;
     }
-    float* Cz = C + (int64_t)blockIdx.z * c_split;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -141,7 +135,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(const uint16_t* __restrict
             for (int r = 0; r < 4; ++r) {
                 const int i = m0 + 16 * a + 4 * (lane >> 4) + r;
                 const int j = n0 + 16 * b + r16;
-                if (i < M && j < N) Cz[(int64_t)i * ldc + j] = acc[a][b][r];
+                if (i < M && j < N) C[(int64_t)i * ldc + j] = acc[a][b][r];
             }
 }
 
@@ -185,11 +179,6 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restri
 }
 
 // ---------------------------------------------------------------- phi
-__device__ inline float layer1_pre(const float* __restrict__ x, const float* __restrict__ W1q,
-                                   const float* __restrict__ b1, int j) {
-    return fmaf(x[2], W1q[3 * j + 2], fmaf(x[1], W1q[3 * j + 1], fmaf(x[0], W1q[3 * j], b1[j])));
-}
-
 // Point range of set s clamped to [0, P) (offsets are caller data; bad
 // offsets make the loss NaN, never an access outside the buffers).
 __device__ inline void set_range(const int64_t* __restrict__ off, int64_t s, int64_t P, int64_t& lo, int64_t& hi) {
@@ -1199,10 +1188,9 @@ inline int grid_for(int64_t n, int per_block = 256, int cap = 65536) {
 }
 
 inline int gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, float* C, int64_t ldc, int M,
-                   int N, int K, int splits, int64_t c_split, hipStream_t st) {
-    const int kchunk = ((K / splits + 31) / 32) * 32;
-    dim3 grid((M + 63) / 64, (N + 63) / 64, splits);
-    hipLaunchKernelGGL(gemm_nt_kernel, grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, kchunk, c_split);
+                   int N, int K, hipStream_t st) {
+    dim3 grid((M + 63) / 64, (N + 63) / 64);
+    hipLaunchKernelGGL(gemm_nt_kernel, grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K);
     return (int)hipGetLastError();
 }
 
@@ -1252,7 +1240,7 @@ int launch_predict(const float* theta, const SgQuant& q, const float* Eq, int64_
                        B, Bpad, w.Z);
     int err = (int)hipGetLastError();
     if (err) return err;
-    err = gemm_nt(w.Z, 3 * H, q.W3, 3 * H, w.PRE3, H, (int)B, H, 3 * H, 1, 0, st);
+    err = gemm_nt(w.Z, 3 * H, q.W3, 3 * H, w.PRE3, H, (int)B, H, 3 * H, st);
     if (err) return err;
     hipLaunchKernelGGL(head_fwd_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, st, w.PRE3, theta, q.w4, B, t_out,
                        pred);
@@ -1281,9 +1269,9 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
     // dW3 = dG^T Z: both transposed to K = pair index
     if ((err = transpose(w.dGq, H, (int)B, (int)Bpad, H, w.dGqT, Bpad, st))) return err;
     if ((err = transpose(w.Z, 3 * H, (int)B, (int)Bpad, 3 * H, w.ZT, Bpad, st))) return err;
-    if ((err = gemm_nt(w.dGqT, Bpad, w.ZT, Bpad, grad + kSgW3, 3 * H, H, 3 * H, (int)Bpad, 1, 0, st))) return err;
+    if ((err = gemm_nt(w.dGqT, Bpad, w.ZT, Bpad, grad + kSgW3, 3 * H, H, 3 * H, (int)Bpad, st))) return err;
     // dZ = dG W3
-    if ((err = gemm_nt(w.dGq, H, q.W3T, H, w.dZ, 3 * H, (int)B, 3 * H, H, 1, 0, st))) return err;
+    if ((err = gemm_nt(w.dGq, H, q.W3T, H, w.dZ, 3 * H, (int)B, 3 * H, H, st))) return err;
     hipLaunchKernelGGL(dz_to_de_kernel, dim3(grid_for(B * H)), dim3(256), 0, st, w.dZ, w.E, B, w.dE);
     if ((err = (int)hipGetLastError())) return err;
     // pooling and both point layers
