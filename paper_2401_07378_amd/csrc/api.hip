@@ -1563,9 +1563,9 @@ nnsemd_status_t nnsemd_sg_predict(nnsemd_handle_t h, const float* theta, const f
 }
 
 namespace {
-// Carve the training workspace for B pairs; returns bytes
+// Carve the training workspace for B pairs and P points; returns bytes
 // needed (base == nullptr: size only).
-static size_t sg_train_carve(char* base, int64_t B, bool own_grad, sg::SgTrainWork& w, float** grad) {
+static size_t sg_train_carve(char* base, int64_t B, int64_t P, bool own_grad, sg::SgTrainWork& w, float** grad) {
     constexpr int64_t Hd = kSgHidden;
     const int64_t Bpad = (B + 63) / 64 * 64, S = 2 * B;
     Carver c;
@@ -1575,7 +1575,7 @@ static size_t sg_train_carve(char* base, int64_t B, bool own_grad, sg::SgTrainWo
     const size_t oPRE3 = c.take(4 * Bpad * Hd), odZ = c.take(4 * Bpad * 3 * Hd);
     const size_t oHB = c.take(4 * Bpad * kSgHbCols), ohs = c.take(4 * kSgHbCols);
     const size_t ot = c.take(4 * Bpad), opred = c.take(4 * Bpad);
-    const size_t opart = c.take(4 * (size_t)std::min<int64_t>(S, kSgTrainGrid) * kSgTrainPart);
+    const size_t opart = c.take(4 * (size_t)sg_train_grid(P) * kSgTrainPart), oset = c.take(4 * (size_t)P);
     const size_t obad = c.take(64);
     const size_t ograd = own_grad ? c.take(4 * kSgParams) : 0;
     if (base != nullptr) {
@@ -1594,6 +1594,7 @@ static size_t sg_train_carve(char* base, int64_t B, bool own_grad, sg::SgTrainWo
         w.t = F(ot);
         w.pred = F(opred);
         w.part = F(opart);
+        w.set_of = reinterpret_cast<int32_t*>(base + oset);
         w.bad = reinterpret_cast<int*>(base + obad);
         if (own_grad) *grad = F(ograd);
     }
@@ -1611,9 +1612,9 @@ static nnsemd_status_t sg_loss_grad_common(nnsemd_handle_t h, const float* theta
     if (s != NNSEMD_OK) return s;
     sg::SgTrainWork w;
     const bool own = *grad == nullptr;
-    const size_t need = sg_train_carve(nullptr, num_pairs, own, w, grad);
+    const size_t need = sg_train_carve(nullptr, num_pairs, num_points, own, w, grad);
     if ((s = sg_workspace(h, need)) != NNSEMD_OK) return s;
-    sg_train_carve(h->sg_ws, num_pairs, own, w, grad);
+    sg_train_carve(h->sg_ws, num_pairs, num_points, own, w, grad);
     const int err = sg::launch_loss_grad(theta, q, X, a, set_off, num_pairs, num_points, labels, w, loss, *grad, stream);
     if (err != 0) return device_fail(h, err, "surrogate backward");
     return NNSEMD_OK;

@@ -259,7 +259,9 @@ constexpr int64_t kSgB4 = kSgW4 + kSgHidden;
 constexpr int64_t kSgParams = kSgB4 + 1;
 constexpr int kSgHbCols = 2 * kSgHidden + 8;  // head-backward row: dg | dt*g | dt | r^2/B | pad
 constexpr int kSgTrainPart = kSgHidden * kSgHidden + 5 * kSgHidden;  // partial gradient of the point layers
-constexpr int kSgTrainGrid = 256;  // workgroups of their backward (one per CU, its LDS), at most: one partial each
+// Workgroups of their backward over P points, one partial each: one per 64-point
+// chunk, at most one per CU (its LDS).
+inline int sg_train_grid(int64_t P) { return (int)(P < 256 * 64 ? (P + 63) / 64 : 256); }
 constexpr int kSgTopkMax = 1024;
 
 namespace sg {
@@ -280,12 +282,14 @@ struct SgTrainWork {
     float *E, *dE;                        // 2B x H
     uint16_t *Z, *ZT, *dGq, *dGqT;        // Bpad x 3H, 3H x Bpad, Bpad x H, H x Bpad
     float *PRE3, *dZ, *HB, *hsum, *t, *pred;
-    float* part;                          // min(2B, kSgTrainGrid) partial gradients of the point layers
+    float* part;                          // sg_train_grid(P) partial gradients of the point layers
+    int32_t* set_of;                      // P: each point's set
     int* bad;  // offsets check
 };
 int launch_prepare(const float* theta, const SgQuant& q, void* stream);
 int launch_embed(const float* theta, const SgQuant& q, const float* X, const float* a, const int64_t* set_off,
-                 int64_t num_sets, int64_t num_points, float* E, void* stream, bool in_order = false);
+                 int64_t num_sets, int64_t num_points, float* E, void* stream, int32_t* set_of = nullptr);
+// (set_of: the training forward, points summed in index order; receives each point's set)
 int launch_predict(const float* theta, const SgQuant& q, const float* Eq, int64_t nq, const float* Ec, int64_t nc,
                    const int32_t* qi, const int32_t* ci, int train_layout, int64_t B, const SgPredictWork& w,
                    float* t_out, float* pred, void* stream);

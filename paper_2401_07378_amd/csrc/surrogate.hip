@@ -241,7 +241,7 @@ __device__ inline void layer1_tile(const float4* xs, int np, const float (&w)[2]
 // Fused inference: persistent workgroups, each walking the 64-point chunks of
 // its sets: layer 1 into LDS (BF16), layer 2 on the matrix cores (each
 // wavefront 64 points x 64 outputs, its 32 KB of W2 held in 128 registers for
-// the whole launch), bias + ReLU + mass weighting, column sums in registers.
+// the whole launch; 14 to 16 other values of a lane are spilled), bias + ReLU + mass weighting, column sums in registers.
 // The next chunk's points are loaded while the current one multiplies.
 // Bound: a chunk is 2.0 k cycles of matrix pipe per SIMD; the vector work
 // (layer 1 about 350 instructions a thread with the packed BF16 conversion,
@@ -252,11 +252,11 @@ __device__ inline void layer1_tile(const float4* xs, int np, const float (&w)[2]
 // SEQ: the points of a set are added one after the other in index order (the
 // training forward's definition; its BF16 pair features would otherwise round
 // some values the other way): the sum passes through the four 16-lane groups
-// of a block in row order.
+// of a block in row order.  It also notes each point's set for the backward.
 template <bool SEQ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void embed_fused_kernel(
     const float* __restrict__ X, const float* __restrict__ a, const int64_t* __restrict__ off, int64_t S, int64_t P,
-    SgQuant q, const float* __restrict__ theta, float* __restrict__ E) {
+    SgQuant q, const float* __restrict__ theta, float* __restrict__ E, int32_t* __restrict__ set_of) {
     constexpr int LD = H + 8;  // padded row (elements) against bank conflicts
     __shared__ __align__(16) uint16_t h1[64 * LD];
     __shared__ float4 xs[2][64];
@@ -287,7 +287,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void e
     auto fetch = [&]() {
         pre = make_float4(0.f, 0.f, 0.f, 0.f);
         const int64_t p = it.p0 + tid;
-        if (tid < 64 && it.s < S && p < it.hi) pre = make_float4(X[3 * p], X[3 * p + 1], X[3 * p + 2], a[p]);
+        if (tid < 64 && it.s < S && p < it.hi) {
+            pre = make_float4(X[3 * p], X[3 * p + 1], X[3 * p + 2], a[p]);
+            if constexpr (SEQ) set_of[p] = (int32_t)it.s;
+        }
     };
     fetch();
     float colsum[4] = {0.f, 0.f, 0.f, 0.f};  // column 64 wave + 16 b + r16, after the lane reduction
@@ -594,8 +597,10 @@ __global__ void dz_to_de_kernel(const float* __restrict__ dZ, const float* __res
     }
 }
 
-// Backward of pooling and both point layers, fused: persistent workgroups walk
-// the 64-point chunks of their sets.  Per chunk, everything stays on chip:
+// Backward of pooling and both point layers, fused: persistent workgroups take
+// every gridDim.x-th chunk of 64 consecutive points, whatever sets they are in
+// (set_of), so few large sets fill the chip and many small ones leave no row
+// idle.  Per chunk, everything stays on chip:
 //   layer 1 again into LDS (BF16), in point-major and unit-major order;
 //   PRE2 = H1 W2^T again on the matrix cores (same products in the same order
 //   as the forward), dP2 = a dE where PRE2 + b2 > 0, rounded to BF16 into LDS
@@ -606,15 +611,19 @@ __global__ void dz_to_de_kernel(const float* __restrict__ dZ, const float* __res
 // One partial gradient per workgroup, summed by train_reduce_kernel in order.
 // Before, PRE2, dP2, dH1 and two transposes went through memory (about 1.5 KB
 // a point each way) in nine launches.  Bound: matrix pipe and the W2 / W2^T
-// fragments from L2 (256 KB a chunk).  A step of 512 pairs of 256-point
-// clouds: 1780 -> 414 us.
+// fragments from L2 (256 KB a chunk); 35 of a lane's values are spilled.  A step
+// of 512 pairs of 256-point clouds: 1780 -> 405 us.  Chunks within a set, dealt
+// set by set, against chunks of the point array: 2 sets of 100000 points 31.2 ->
+// 6.8 ms (what is left is the forward, which adds a set's points in order),
+// 131072 sets of one point 13.4 -> 5.3 ms (unfused 7.5), 512 pairs of 40..80
+// points 262 -> 202 us, whole sets of 64 or 256 the same.
 constexpr int kTrainThreads = 512;
 constexpr int kTrainLd = H + 8, kTrainLdT = 64 + 8;
 constexpr size_t kTrainLds = 2 * sizeof(uint16_t) * (64 * (size_t)kTrainLd + H * (size_t)kTrainLdT);
 // partial: dW2 (H x H), dW1 (H x 3), db1 (H), db2 (H)
 constexpr int kTrainPart = kSgTrainPart;
 __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2))) void train_bwd_kernel(
-    const float* __restrict__ X, const float* __restrict__ a, const int64_t* __restrict__ off, int64_t S, int64_t P,
+    const float* __restrict__ X, const float* __restrict__ a, const int32_t* __restrict__ set_of, int64_t S, int64_t P,
     SgQuant q, const float* __restrict__ theta, const float* __restrict__ dE, float* __restrict__ part) {
     extern __shared__ __align__(16) uint16_t lds16[];
     uint16_t* h1 = lds16;
@@ -622,6 +631,7 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
     uint16_t* h1T = dp + 64 * kTrainLd;
     uint16_t* dpT = h1T + H * kTrainLdT;
     __shared__ float4 xs[2][64];
+    __shared__ int sid[2][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g4 = lane >> 4, kq = 8 * g4;
     const int unit = tid & (H - 1), ph = 32 * (tid >> 8);  // layer 1: one unit, 32 points
@@ -645,13 +655,19 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int j = 0; j < 8; ++j) dw[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     float db2[2] = {0.f, 0.f}, gb[2] = {0.f, 0.f}, gw[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
-    ChunkWalk it;
-    it.start(off, S, P, blockIdx.x);
+    int64_t p0 = 64 * (int64_t)blockIdx.x;
     float4 pre = make_float4(0.f, 0.f, 0.f, 0.f);
+    int presid = 0;
     auto fetch = [&]() {
         pre = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int64_t p = it.p0 + tid;
-        if (tid < 64 && it.s < S && p < it.hi) pre = make_float4(X[3 * p], X[3 * p + 1], X[3 * p + 2], a[p]);
+        if (tid < 64) {
+            const int64_t p = min(p0 + tid, P - 1);
+            if (p0 + tid < P) pre = make_float4(X[3 * p], X[3 * p + 1], X[3 * p + 2], a[p]);
+            // offsets that are no partition leave points without a set: any row
+            // in bounds will do (the loss is NaN then)
+            const int id = set_of[p];
+            presid = id >= 0 && id < S ? id : 0;
+        }
     };
     auto product = [&](f32x4 (&acc)[4][2], const uint16_t* A, const uint16_t* B) {
 #pragma unroll
@@ -659,7 +675,7 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[i][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
         // W fragments two K steps ahead; a rolled loop (unrolled, the compiler
-        // keeps all sixteen in flight and spills)
+        // keeps all sixteen in flight and spills more)
         bf16x8 b0[2], b1n[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -687,12 +703,17 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
     };
     fetch();
     int buf = 0;
-    while (it.s < S) {
-        if (tid < 64) xs[buf][tid] = pre;
-        const float de[2] = {dE[it.s * H + colv[0]], dE[it.s * H + colv[1]]};
+    while (p0 < P) {
+        if (tid < 64) {
+            xs[buf][tid] = pre;
+            sid[buf][tid] = presid;
+        }
         __syncthreads();  // also: every wavefront is done with the LDS tiles
-        it.next(off, S, P, gridDim.x);
-        fetch();
+        p0 += 64 * (int64_t)gridDim.x;
+        if (p0 < P) fetch();
+        const int s0 = sid[buf][0];
+        const bool one_set = s0 == sid[buf][63];  // sets are in ascending order
+        const float de[2] = {dE[(int64_t)s0 * H + colv[0]], dE[(int64_t)s0 * H + colv[1]]};
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             uint32_t pk[4];
@@ -713,27 +734,43 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
         __syncthreads();
         f32x4 acc[4][2];
         product(acc, h1, q.W2);
+        auto dp2 = [&](int i, int b, const float (&der)[4]) {
+            uint32_t pk[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int e = 0; e < 2; ++e) {
+                const int pr = 16 * i + 4 * g4 + 2 * e;
+                float v[2];
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                uint32_t pk[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    float v[2];
-#pragma unroll
-                    for (int w = 0; w < 2; ++w) {
-                        const int pr = 16 * i + 4 * g4 + 2 * e + w;
-                        v[w] = acc[i][b][2 * e + w] + b2v[b] > 0.f ? xs[buf][pr].w * de[b] : 0.f;
-                        db2[b] += v[w];
-                    }
-                    pk[e] = pack_bf16(v[0], v[1]);
-                    const int pr = 16 * i + 4 * g4 + 2 * e;
-                    dp[pr * kTrainLd + colv[b]] = (uint16_t)pk[e];
-                    dp[(pr + 1) * kTrainLd + colv[b]] = (uint16_t)(pk[e] >> 16);
+                for (int w = 0; w < 2; ++w) {
+                    v[w] = acc[i][b][2 * e + w] + b2v[b] > 0.f ? xs[buf][pr + w].w * der[2 * e + w] : 0.f;
+                    db2[b] += v[w];
                 }
-                *reinterpret_cast<uint2*>(&dpT[colv[b] * kTrainLdT + 16 * i + 4 * g4]) = make_uint2(pk[0], pk[1]);
+                pk[e] = pack_bf16(v[0], v[1]);
+                dp[pr * kTrainLd + colv[b]] = (uint16_t)pk[e];
+                dp[(pr + 1) * kTrainLd + colv[b]] = (uint16_t)(pk[e] >> 16);
             }
+            *reinterpret_cast<uint2*>(&dpT[colv[b] * kTrainLdT + 16 * i + 4 * g4]) = make_uint2(pk[0], pk[1]);
+        };
+        if (one_set) {  // workgroup-uniform
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const float der[4] = {de[b], de[b], de[b], de[b]};
+                    dp2(i, b, der);
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    float der[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        der[r] = dE[(int64_t)sid[buf][16 * i + 4 * g4 + r] * H + colv[b]];
+                    dp2(i, b, der);
+                }
+        }
         __syncthreads();
         product(acc, dp, q.W2T);
 #pragma unroll
@@ -1210,16 +1247,16 @@ int launch_prepare(const float* theta, const SgQuant& q, void* stream) {
 }
 
 int launch_embed(const float* theta, const SgQuant& q, const float* X, const float* a, const int64_t* set_off,
-                 int64_t num_sets, int64_t num_points, float* E, void* stream, bool in_order) {
+                 int64_t num_sets, int64_t num_points, float* E, void* stream, int32_t* set_of) {
     if (num_sets == 0) return 0;
     // two resident workgroups per CU (their registers), each walking its share of the sets
     const unsigned grid = (unsigned)std::min<int64_t>(num_sets, 512);
-    if (in_order)
+    if (set_of != nullptr)
         hipLaunchKernelGGL(embed_fused_kernel<true>, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, a, set_off,
-                           num_sets, num_points, q, theta, E);
+                           num_sets, num_points, q, theta, E, set_of);
     else
         hipLaunchKernelGGL(embed_fused_kernel<false>, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, a, set_off,
-                           num_sets, num_points, q, theta, E);
+                           num_sets, num_points, q, theta, E, set_of);
     return (int)hipGetLastError();
 }
 
@@ -1256,7 +1293,7 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
     int err;
     hipLaunchKernelGGL(check_offsets_kernel, dim3(1), dim3(256), 0, st, set_off, S, P, w.bad);
     // forward: the inference kernel
-    if ((err = launch_embed(theta, q, X, a, set_off, S, P, w.E, stream, true))) return err;
+    if ((err = launch_embed(theta, q, X, a, set_off, S, P, w.E, stream, w.set_of))) return err;
     SgPredictWork pw{w.Z, w.PRE3};
     if ((err = launch_predict(theta, q, w.E, S, w.E, S, nullptr, nullptr, 1, B, pw, w.t, w.pred, stream))) return err;
     // head backward
@@ -1275,11 +1312,11 @@ int launch_loss_grad(const float* theta, const SgQuant& q, const float* X, const
     hipLaunchKernelGGL(dz_to_de_kernel, dim3(grid_for(B * H)), dim3(256), 0, st, w.dZ, w.E, B, w.dE);
     if ((err = (int)hipGetLastError())) return err;
     // pooling and both point layers
-    const int grid = (int)std::min<int64_t>(S, kSgTrainGrid);
+    const int grid = sg_train_grid(P);
     err = (int)hipFuncSetAttribute((const void*)train_bwd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)kTrainLds);
     if (err) return err;
-    hipLaunchKernelGGL(train_bwd_kernel, dim3(grid), dim3(kTrainThreads), kTrainLds, st, X, a, set_off, S, P, q, theta,
+    hipLaunchKernelGGL(train_bwd_kernel, dim3(grid), dim3(kTrainThreads), kTrainLds, st, X, a, w.set_of, S, P, q, theta,
                        w.dE, w.part);
     if ((err = (int)hipGetLastError())) return err;
     static_assert(kTrainPart % 64 == 0, "whole workgroups");

@@ -304,3 +304,22 @@ def test_gradient_chunk_edges(pairs, sizes):
     wl, wg = SO.loss_and_grad(th, X, a, off, y, rounding=True)
     assert float(loss.item()) == pytest.approx(float(wl), rel=1e-3)
     _close_blockwise(grad.cpu().numpy(), wg, 2e-2)
+
+
+@pytest.mark.parametrize("pairs,sizes", [(2, [1, 0, 2, 1]), (40, [0, 1, 2, 7, 0, 30]), (32, [64, 1, 63, 65]),
+                                         (4097, [2]), (2, [9000, 7400, 1, 3])],
+                         ids=["tiny", "empty", "straddling", "past-one-round", "few-large"])
+def test_gradient_chunks_across_sets(pairs, sizes):
+    """The backward's 64-point chunks hold points of several sets, empty sets
+    lie between them, and a workgroup takes a second chunk (more than 256 x 64
+    points); two calls give the same bits."""
+    from paper_2401_07378_amd import binding
+    X, a, off = _sets(pairs, [sizes[k % len(sizes)] for k in range(2 * pairs)])
+    th = _theta(6)
+    y = W.to_f32(np.random.default_rng(pairs).uniform(0.1, 1.0, pairs))
+    loss, grad = binding.sg_loss_grad(to_dev(th), to_dev(X), to_dev(a), to_dev(off), to_dev(y))
+    wl, wg = SO.loss_and_grad(th, X, a, off, y, rounding=True)
+    assert float(loss.item()) == pytest.approx(float(wl), rel=1e-3)
+    _close_blockwise(grad.cpu().numpy(), wg, 2e-2)
+    again = binding.sg_loss_grad(to_dev(th), to_dev(X), to_dev(a), to_dev(off), to_dev(y))[1]
+    assert np.array_equal(grad.cpu().numpy(), again.cpu().numpy())
