@@ -28,6 +28,22 @@ def test_chunk_edges(mn, lattice, protocol):
         assert_pair_matches(g, oracle_pair(X, a, Y, b, protocol=protocol, seed=3), label=f"{mn}-{lattice}-{threads}")
 
 
+@pytest.mark.parametrize("mn", [(1025, 1024), (1300, 2048), (2049, 700), (2300, 2560), (3072, 400), (3073, 64),
+                                (300, 4096)], ids=lambda v: "%dx%d" % v)
+@pytest.mark.parametrize("metric,protocol,lattice", [("l2", "greedy", 0), ("l2", "random", 40), ("l1", "greedy", 40),
+                                                     ("l1", "random", 0)])
+def test_points_per_thread(mn, metric, protocol, lattice):
+    """Sides around the capacities of the workgroup's variants (4, 8, 12 and
+    16 points per thread of 256; 2, 4 and 8 of 512), beyond one per thread."""
+    m, n = mn
+    X, a, Y, b = W.random_pair(500 + m + 3 * n + lattice, m, n, 2, masses="integer" if lattice else "dirichlet",
+                               lattice=lattice)
+    ref = oracle_pair(X, a, Y, b, metric, protocol=protocol, seed=4)
+    for threads in (256, 512):
+        g = gpu_pair(X, a, Y, b, metric, protocol=protocol, seed=4, threads=threads, path="on_chip")
+        assert_pair_matches(g, ref, label=f"{mn}-{threads}")
+
+
 @pytest.mark.parametrize("metric", ["l2", "sqeuclidean", "l1"])
 def test_one_hub_supplier(metric):
     """Every consumer's nearest supplier is the same one, on an integer ring
