@@ -290,13 +290,15 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 // used here: its back-edge merges with the thread-0-only result write, and
 // the structurized code lets lanes 1-63 of wave 0 pass the following
 // barrier without the fetch, re-solving the same pair forever.)
-// Register budget, up to four claimants per thread, chosen so that no
-// variant spills: 128 VGPRs for d <= 3 (four waves per SIMD, so small
-// pairs keep four workgroups per CU), 168 for d = 4, 5 and 256 for d = 6, 7,
-// whose larger LDS records hold a 1024-point pair to two or three
-// workgroups per CU anyway.
+// Register budget, up to four points per thread and side: 128 VGPRs for d <= 3
+// (four waves per SIMD, so small pairs keep four workgroups per CU), 168 for
+// d = 4, 5 and 256 for d = 6, 7, whose larger LDS records hold a 1024-point pair
+// to two or three workgroups per CU anyway; no variant spills with these.  Two
+// points per thread of 512 (1024 pairs of 128..1024 points, d = 3): held to 80
+// VGPRs, 27 to 32 registers of the matrix-core search spill, 557 us, with 128
+// 503; the L1 search spills 4 to 10 with 80, 506 us, none with 96, 522.
 template <int D, int T, int CSMAX, bool L1, bool CL>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 && L1 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
 void pair_solver_kernel(PairSolverArgs A) {
     extern __shared__ __align__(16) char lds_dyn[];
     __shared__ SharedCore sh;
