@@ -219,7 +219,7 @@ __device__ void solve_cost_pair(const CostArgs& A, int64_t p, const Lds16& L, Sh
             }
         }
         __syncthreads();
-        constexpr bool pack = sizeof(TD) == 4;  // FP32 entries leave room for the index
+        const bool pack = sizeof(TD) == 4 && A.protocol == NNSEMD_GREEDY;  // FP32 entries leave room for the index
         round_buckets_pos<T, CSMAX>(L, sh, mact, nact, pack);
         // keys are the distances themselves (metric code SQEUCLIDEAN: D = key)
         round_rank_pos<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, pack);

@@ -242,10 +242,11 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
         NNSEMD_PH(2)
 
         // ---- 2. claimant sets a_i (exact keys leave room for the index)
-        round_buckets_pos<T, CSMAX>(L, sh, mact, nact, exact);
+        const bool pack = exact && A.protocol == NNSEMD_GREEDY;
+        round_buckets_pos<T, CSMAX>(L, sh, mact, nact, pack);
         NNSEMD_PH(3)
         // ---- 3. flow & cost: claimant order, then the serve walk
-        round_rank_pos<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, exact);
+        round_rank_pos<T, CSMAX>(L, nact, A.protocol, A.seed, rounds, pack);
         NNSEMD_PH(5)
         round_walk_pos<T>(L, mact);
         NNSEMD_PH(6)

@@ -499,8 +499,9 @@ __device__ inline double unpack_key(double k) {
     return __longlong_as_double(__double_as_longlong(k) & ~(long long)kPackMask);
 }
 
-// ---- claimant sets a_i in bucket order.  pack: see pack_key; the keys of
-// buckets with two or more members are left packed for round_rank_pos.
+// ---- claimant sets a_i in bucket order.  pack (greedy protocol): see pack_key;
+// the keys of buckets with two or more members are left packed for
+// round_rank_pos.
 template <int T, int CS, typename LT>
 __device__ inline void round_buckets_pos(const LT& L, SharedCore& sh, int mact, int nact, bool pack) {
     constexpr int NW = T / kWave;
@@ -567,18 +568,33 @@ __device__ inline void round_buckets_pos(const LT& L, SharedCore& sh, int mact, 
 
 // ---- serve order inside each bucket: a claimant's rank is the number of
 // members below it, counted over consecutive keys that all members of the
-// bucket read together.
+// bucket read together.  Random protocol: each claimant's random key is drawn
+// once and takes the place of its distance key (held in a register meanwhile)
+// for the count, instead of being drawn again by every member of the bucket.
 template <int T, int CS, typename LT>
 __device__ inline void round_rank_pos(const LT& L, int nact, int protocol, uint64_t seed, int rounds, bool pack) {
     const int tid = threadIdx.x;
     int np[CS], jv[CS];
     double kv[CS];
+    if (protocol != NNSEMD_GREEDY) {
+#pragma unroll
+        for (int u = 0; u < CS; ++u) {
+            const int p = u * T + tid;
+            kv[u] = 0.0;
+            if (p < nact && L.scnt[L.cnn[p]] > 1) {
+                const int j = L.list[p];
+                kv[u] = L.ckey[p];
+                // the random order is drawn for the caller's consumer indices
+                L.ckey[p] = __longlong_as_double((long long)rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j] : j));
+            }
+        }
+        __syncthreads();
+    }
 #pragma unroll
     for (int u = 0; u < CS; ++u) {
         const int p = u * T + tid;
         np[u] = -1;
         jv[u] = 0;
-        kv[u] = 0.0;
         if (p >= nact) continue;
         const int sl = L.cnn[p];
         const int c = L.scnt[sl];
@@ -586,31 +602,33 @@ __device__ inline void round_rank_pos(const LT& L, int nact, int protocol, uint6
         const int end = L.soff[sl], start = end - c;
         const int j = L.list[p];
         const double k = L.ckey[p];
-        int rank = 0;
+        int rank = 0, le = 0;
         if (protocol == NNSEMD_GREEDY) {
-            int le = 0;
 #pragma unroll 4
             for (int e = start; e < end; ++e) {
                 const double k2 = L.ckey[e];
                 rank += k2 < k;
                 le += k2 <= k;
             }
-            if (le - rank > 1) {  // equal keys: by consumer index
-                for (int e = start; e < end; ++e) rank += L.ckey[e] == k && L.list[e] < j;
-            }
+            kv[u] = pack ? unpack_key(k) : k;
         } else {
-            // the random order is drawn for the caller's consumer indices
-            const uint64_t r = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j] : j);
+            const uint64_t r = (uint64_t)__double_as_longlong(k);
 #pragma unroll 4
             for (int e = start; e < end; ++e) {
-                const int j2 = L.list[e];
-                const uint64_t r2 = rp_key(seed, rounds, L.jmap != nullptr ? L.jmap[j2] : j2);
-                rank += (r2 < r) || (r2 == r && j2 < j);
+                const uint64_t r2 = (uint64_t)__double_as_longlong(L.ckey[e]);
+                rank += r2 < r;
+                le += r2 <= r;
+            }
+        }
+        if (le - rank > 1) {  // equal keys: by consumer index
+            const long long kb = __double_as_longlong(k);
+            for (int e = start; e < end; ++e) {
+                const double k2 = L.ckey[e];
+                rank += (protocol == NNSEMD_GREEDY ? k2 == k : __double_as_longlong(k2) == kb) && L.list[e] < j;
             }
         }
         np[u] = start + rank;
         jv[u] = j;
-        kv[u] = pack ? unpack_key(k) : k;
     }
     __syncthreads();
 #pragma unroll
