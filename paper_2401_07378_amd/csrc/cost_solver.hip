@@ -16,6 +16,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "internal.hpp"
 #include "round_common.hpp"
 
@@ -28,6 +30,16 @@ template <typename TD>
 __device__ inline bool bad_entry(TD v) {
     return !(v >= (TD)0) || !isfinite(v);
 }
+
+// Entries of D in flight per lane of the search, 4 -> 16: 1024 pairs of 64..512
+// points, with the check of D at 8 in flight, FP32 662 -> 299 us, FP64 808 ->
+// 556; 256 pairs of 1025..2048 points, FP64, 10.7 -> 3.8 ms (8: 4.4).  Pairs of
+// at most 256 points a side have a variant of their own, with 8: many of
+// them together are short of wavefronts rather than of loads in flight (8192 pairs of 8..64
+// points, FP64: 4 in flight 352 us; 16, four points per thread 447; 16, one
+// point 318; 8 285).
+template <typename TD, int CSMAX>
+constexpr int kCostUnroll = CSMAX == 1 ? 8 : 16;
 
 template <typename TD, int T, int CSMAX>
 __device__ void solve_cost_pair(const CostArgs& A, int64_t p, const Lds16& L, SharedCore& sh) {
@@ -174,31 +186,27 @@ __device__ void solve_cost_pair(const CostArgs& A, int64_t p, const Lds16& L, Sh
             const int j = L.cact[valid ? q : 0];
             TD b1 = (TD)INFINITY, b2 = (TD)INFINITY;
             int bs = 0x7fffffff;
-            // 16 entries in flight per lane: the scan is bound by load latency (1024
-            // pairs of 64..512 points, FP32, with the check above at 8 in flight: 4 ->
-            // 16 entries 679 -> 360 us)
-            constexpr int U = 16;
-            const int stride = S * U;
-            const int full = (mact / stride) * stride;
-            for (int s0 = r; s0 < full; s0 += stride) {
-                TD k[U];
+            // UMAX entries in flight per lane while that many are left, then four:
+            // the scan is bound by load latency (see kCostUnroll)
+            auto scan = [&](auto in_flight, int s0) {
+                constexpr int U = decltype(in_flight)::value;
+                for (; s0 + (U - 1) * S < mact; s0 += U * S) {
+                    TD k[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) k[u] = D[(int64_t)L.sidx[s0 + u * S] * ni + j];
+                    for (int u = 0; u < U; ++u) k[u] = D[(int64_t)L.sidx[s0 + u * S] * ni + j];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool lt = k[u] < b1;
-                    bs = lt ? s0 + u * S : bs;
-                    b2 = lt ? b1 : (k[u] < b2 ? k[u] : b2);
-                    b1 = lt ? k[u] : b1;
+                    for (int u = 0; u < U; ++u) {
+                        const bool lt = k[u] < b1;
+                        bs = lt ? s0 + u * S : bs;
+                        b2 = lt ? b1 : (k[u] < b2 ? k[u] : b2);
+                        b1 = lt ? k[u] : b1;
+                    }
                 }
-            }
-            for (int s = full + r; s < mact; s += S) {
-                const TD k = D[(int64_t)L.sidx[s] * ni + j];
-                const bool lt = k < b1;
-                bs = lt ? s : bs;
-                b2 = lt ? b1 : (k < b2 ? k : b2);
-                b1 = lt ? k : b1;
-            }
+                return s0;
+            };
+            int s0 = scan(std::integral_constant<int, kCostUnroll<TD, CSMAX>>{}, r);
+            s0 = scan(std::integral_constant<int, 4>{}, s0);
+            scan(std::integral_constant<int, 1>{}, s0);
             for (int o = 1; o < S; o <<= 1) {
                 const TD c1 = __shfl_xor(b1, o);
                 const TD c2 = __shfl_xor(b2, o);
@@ -362,6 +370,9 @@ int launch_l1_tiles(const DocArgs& A, bool bf16, double* tiles, int64_t tile_str
 
 int launch_cost_solver(const CostArgs& A, bool f64, int chunk_max, size_t lds, int grid, void* stream, int* blocks) {
     hipStream_t st = (hipStream_t)stream;
+    if (chunk_max <= 1)
+        return f64 ? launch_typed<double, 256, 1>(A, lds, grid, st, blocks)
+                   : launch_typed<float, 256, 1>(A, lds, grid, st, blocks);
     if (chunk_max <= 4)
         return f64 ? launch_typed<double, 256, 4>(A, lds, grid, st, blocks)
                    : launch_typed<float, 256, 4>(A, lds, grid, st, blocks);

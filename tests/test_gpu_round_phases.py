@@ -138,3 +138,28 @@ def test_given_d_ties(mn, dtype):
     assert int(st["near_ties_nn"]) == ref["near_ties_nn"]
     assert int(st["near_ties_order"]) == ref["near_ties_order"]
     assert float(r["cost"].item()) == pytest.approx(ref["cost"], rel=1e-12)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("protocol", ["greedy", "random"])
+@pytest.mark.parametrize("mn", [(1, 1), (7, 256), (16, 64), (19, 130), (256, 31), (256, 256), (257, 40)],
+                         ids=lambda v: "%dx%d" % v)
+def test_given_d_scan_steps(mn, protocol, dtype):
+    """Supplier counts around the steps of the search (8 or 16 entries per lane,
+    4, 1) and sides around the one-point-per-thread variant."""
+    import torch
+    from paper_2401_07378_amd import binding
+    m, n = mn
+    rng = np.random.default_rng(3 * m + n)
+    D = (rng.random((m, n)) * 4).astype(dtype)
+    a, b = W.dirichlet_masses(rng, m), W.dirichlet_masses(rng, n)
+    r = binding.emd_approx_cost(to_dev(D), to_dev(a), to_dev(b), protocol=protocol, seed=6)
+    torch.cuda.synchronize()
+    st = binding.stats_numpy(r["stats"])[0]
+    ref = oracle.solve_cost(D, a, b, protocol=protocol, seed=6)
+    k = int(st["nnz"])
+    assert st["status"] == 0 and k == ref["nnz"] and int(st["rounds"]) == ref["rounds"]
+    assert np.array_equal(r["plan_src"][:k].cpu().numpy(), ref["src"])
+    assert np.array_equal(r["plan_dst"][:k].cpu().numpy(), ref["dst"])
+    assert np.array_equal(r["plan_flow"][:k].cpu().numpy(), ref["flow"])
+    assert float(r["cost"].item()) == pytest.approx(ref["cost"], rel=1e-12)
