@@ -74,10 +74,10 @@ typedef enum { NNSEMD_F32 = 0, NNSEMD_BF16 = 1, NNSEMD_F64 = 2 } nnsemd_dtype_t;
  * output of the counter (seed, round, consumer), see nnsemd_options_t. */
 typedef enum { NNSEMD_GREEDY = 0, NNSEMD_RANDOM = 1 } nnsemd_protocol_t;
 
-/* Arithmetic of the distance search.  FP32 (FP32 points): FP32 keys on the
- * vector ALUs.  BF16_MFMA_REFINE (BF16 points): the key tile
- * ||x||^2 - 2 x.y of a pair from BF16 matrix-core products with FP32
- * accumulation.  In both modes a consumer whose two best FP32 keys are
+/* Arithmetic of the distance search.  FP32 (FP32 points): FP32 keys, from the
+ * vector ALUs or the FP32 matrix instruction.  BF16_MFMA_REFINE (BF16 points):
+ * the key tile ||x||^2 - 2 x.y of a pair from BF16 matrix-core products with
+ * FP32 accumulation.  In both modes a consumer whose two best FP32 keys are
  * closer than the proven FP32 error bound is re-scored in FP64 from the
  * inputs, so every argmin and every serve order is the one of the FP64
  * definition (ties to the smallest index) and the cost is summed in FP64.

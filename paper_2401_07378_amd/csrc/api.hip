@@ -344,7 +344,7 @@ nnsemd_status_t run_large(nnsemd_handle_t h, LPArgs& A, int d, void* stream) {
 }
 
 // High-dimensional path: BF16 points on the matrix cores, or FP32 points
-// with d > 7 on the vector ALUs.  Pairs are launched in chunks whose key
+// with d > 7.  Pairs are launched in chunks whose key
 // tiles fit the scratch budget.
 constexpr size_t kDocTileBudget = (size_t)4 << 30;
 constexpr int kDocMaxSide = 4096;

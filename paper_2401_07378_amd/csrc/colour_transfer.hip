@@ -8,7 +8,8 @@
 //   assign     argmin_k sum_c (p_c - C_kc)^2 in FP64, channels in order, no
 //              fused multiply-add, ties to the smallest k: an FP32 scan finds
 //              the best two and the FP64 distances decide when the two are
-//              within the scan's error bound (km_assign)
+//              within the scan's error bound (km_assign); small images with
+//              small palettes take the FP64 distances alone
 //   accumulate integer channel sums and counts per cluster: 64-bit integer
 //              atomics, first into a per-workgroup LDS table, then one
 //              global add per cluster and workgroup -- integer sums are the
@@ -44,9 +45,10 @@ __host__ __device__ inline int km_pad(int K) { return (K + 15) & ~15; }
 // centroid); with finite keys they would leave every background pixel open in
 // every pass (two 1024 x 1024 images, three quarters white, 10 update steps:
 // K = 16 5570 us so, 752 with this; K = 256 7730 and 1209; FP64 distances to
-// every centroid, before the scan, took 1075 and 2425).  look: whether there may be equal ones; they meet in a hash table
-// (at most half full, linear probing, so every probe ends).  Not called when
-// the centroids themselves are compared (km_assign_direct; rec null).
+// every centroid, before the scan, took 1075 and 2425).  look: whether there may
+// be equal ones; they meet in a hash table (at most half full, linear probing,
+// so every probe ends).  Not called when the centroids themselves are compared
+// (km_assign_direct; rec null).
 __device__ void km_records(int K, bool look, double c0, double c1, double c2, float4* __restrict__ rec) {
 #pragma clang fp contract(off)
     __shared__ double cc[3 * kKmMax];

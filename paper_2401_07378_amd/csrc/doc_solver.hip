@@ -5,8 +5,9 @@
 // same for every supplier and drops out of the search).  With BF16 inputs the
 // m x n dot products run on the matrix cores (v_mfma_f32_16x16x32_bf16, FP32
 // accumulation; each wavefront computes 32 x 32 output tiles from 2 x 2
-// MFMA blocks); with FP32 inputs they run on the vector ALUs.  The tile goes
-// to a per-workgroup global scratch slot that the rounds read.
+// MFMA blocks); with FP32 inputs on the FP32 matrix instruction (batches) or
+// the vector ALUs (few pairs).  The tile goes to a per-workgroup global scratch
+// slot that the rounds read.
 //
 // Exactness.  Products of BF16 (and the FP32 products fused into FMAs) are
 // exact; every addition is taken to round with error at most 2u (u = 2^-24),
@@ -1675,7 +1676,7 @@ __global__ __launch_bounds__(T, SPLIT ? 5 : 1) void doc_pair_kernel(DocArgs A) {
     float* yn = yy + A.max_n;
     float* kap = yn + A.max_n;
     int32_t* amb = reinterpret_cast<int32_t*>(kap + A.max_n);
-    // FP32 vector tile: its LDS staging panels after the pair's arrays
+    // blocked FP32 tile: its LDS staging panels after the pair's arrays
     float* vstage = reinterpret_cast<float*>(align_up(reinterpret_cast<uintptr_t>(amb + A.max_n), 16));
     const int64_t b = A.pair_base + (int64_t)blockIdx.x;
     const int64_t p = A.order != nullptr ? (int64_t)A.order[b] : b;
@@ -1724,7 +1725,7 @@ int doc_launch_typed(const DocArgs& A, size_t lds, int grid, hipStream_t st, boo
 
 // Compact pair layout (16-bit indices, no records, its own serve-order
 // array) + xx[M], yy[N], yn[N], kap[N] (float), amb[N] (int32), and for FP32
-// points the staging panels of the vector tile (16-byte aligned).
+// points the staging panels of the blocked tile (16-byte aligned).
 size_t doc_lds_bytes(int max_m, int max_n, bool fp32_points) {
     return pair_lds_layout(max_m, max_n, 0, 0, true, false).total +
            sizeof(float) * ((size_t)max_m + 4 * (size_t)max_n) + (fp32_points ? kMmaStageBytes + 16 : 0);

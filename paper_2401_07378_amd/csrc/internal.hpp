@@ -12,8 +12,9 @@ namespace nnsemd {
 // Unit roundoff of FP32 (2^-24).
 constexpr float kU32 = 5.9604644775390625e-08f;
 
-// Record stride (floats) of one active supplier in LDS for dimension d:
-// Euclidean metrics store (-2 x_0 .. -2 x_{d-1}, ||x||^2), L1 stores x.
+// Record stride (floats) of one active supplier for dimension d.  In LDS the
+// coordinates as given and, for the Euclidean metrics, the centred squared norm;
+// the grid-wide path's records in memory hold (-2 x^, ||x^||^2) and, for L1, x.
 __host__ __device__ constexpr int record_stride(int d) { return d + 1 <= 4 ? 4 : 8; }
 
 // Arguments of the per-pair workgroup solver (low-dimensional FP32 points).

@@ -492,7 +492,6 @@ __global__ __launch_bounds__(kLpThreads) void lp_search(LPArgs A, int split) {
     }
 }
 
-
 // ---------------------------------------------------------------- decide
 // Best / second-best merge of two FP32 partials; equal keys keep the smaller
 // slot, so the result does not depend on the merge order.
@@ -1415,12 +1414,13 @@ int launch_tail_metric(const LPArgs& A, bool l1, size_t lds, hipStream_t st) {
     return l1 ? launch_tail_typed<D, true>(A, lds, st) : launch_tail_typed<D, false>(A, lds, st);
 }
 
-// Hand-over point: both active sets at most 512 points.  The workgroup
-// could hold 2048 a side, but the on-chip claimant order costs O(c) per
-// claimant of a bucket of c, and the colour-transfer pair's late rounds
-// have buckets of hundreds to thousands of claimants (one supplier left
-// among many consumers): handing over at 2048 took that pair from 63.0 to
-// 68.1 ms, at 1024 to 62.0 ms, at 512 to 61.0 ms.
+// Hand-over point: both active sets at most 512 points (the workgroup could
+// hold 2048 a side).  The claimant order costs O(c) per claimant of a bucket of
+// c, and the late rounds of a colour-transfer pair have buckets of hundreds to
+// thousands of claimants (one supplier left among many consumers).  Set with the
+// consumer-major order; with the bucket-major phases, handing over at 512, 1024
+// and 2048 takes a 65536-point pair 43.3, 43.3 and 44.0 ms and a 5003 x 7001
+// pair 5.8, 5.3 and 5.8 ms (three input sets agree), so 1024 is open.
 constexpr int kLpTailHandOver = 512;
 
 int lp_tail_capacity(int d, size_t max_lds) {

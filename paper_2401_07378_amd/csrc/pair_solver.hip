@@ -5,21 +5,25 @@
 // masses, the consumers' current picks and the claimant buckets.  The rounds
 // of Algorithm 1 (Sec. III-A) run as barrier-separated phases without ever
 // leaving the chip:
-//   1. NNS (Alg. 1 NNS step): every active consumer scans the active
-//      supplier records in FP32.  For the Euclidean metrics the record is
-//      (-2 x^, ||x^||^2) with x^ = x - centre, so one key costs d FMAs and
-//      equals ||x^ - y^||^2 - ||y^||^2 up to a rounding bound E_q; best and
-//      second-best keys are tracked and a consumer whose two keys are within
-//      that bound is re-scored in FP64 by a whole wavefront, so every pick
-//      equals the FP64 argmin with ties going to the smallest index.
-//   2. Claimant sets a_i: LDS-atomic counting sort of consumers by pick.
-//   3. Flow & cost (greedy or random protocol): one lane per claimed
-//      supplier selects its claimants in (D_ij, j) order (or the random
-//      protocol's key order) and serves f = min(s_i, c_j) in FP64 with the
-//      same operations as the definition, so flows are bit-identical to it.
+//   1. NNS (Alg. 1 NNS step): every active consumer is compared with the
+//      active supplier records in FP32 (point_search.hpp).  For the Euclidean
+//      metrics the record holds x and ||x^||^2 with x^ = x - centre, and the
+//      key ||x^||^2 - 2 x^.y^ equals ||x^ - y^||^2 - ||y^||^2 up to a rounding
+//      bound E_q; 64 consumers and more are compared on the FP32 matrix
+//      instruction, fewer (and L1) on the vector ALUs.  Best and second-best
+//      keys are tracked and a consumer whose two keys are within that bound is
+//      re-scored in FP64 by a whole wavefront, so every pick equals the FP64
+//      argmin with ties going to the smallest index.
+//   2. Claimant sets a_i: LDS-atomic counting sort of consumers by pick, the
+//      keys and slots moving with them.
+//   3. Flow & cost (greedy or random protocol): every claimant's rank in its
+//      bucket, by (D_ij, j) or the random key; then one lane per claimed
+//      supplier serves its claimants in that order, f = min(s_i, c_j) in FP64
+//      with the same operations as the definition, so flows are bit-identical
+//      to it.
 //   4. Weights update: plan entries and the surviving suppliers/consumers
-//      are compacted with one block-wide prefix scan (ballot-free: per-lane
-//      contiguous chunks, wavefront shuffles, one LDS hop).
+//      are compacted by ballots per (chunk, wavefront) and one scan of their
+//      totals.
 // One launch covers any number of ragged pairs, one workgroup each (the
 // batching of Sec. III-D without padding).
 #include <hip/hip_runtime.h>
@@ -90,7 +94,6 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
     const float* __restrict__ Yg = A.Y + y0 * D;
     const int mi = (int)m, ni = (int)n;
     // consumer coordinates for the rounds (LDS copies in the CL variant, filled below)
-    const float* __restrict__ X = Xg;
     const float* __restrict__ Y = CL ? L.yl : Yg;
 
     // ------------------------------------- ingest: masses, checks, bounding box
@@ -178,7 +181,7 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
             if (L1) {
 #pragma unroll
                 for (int t = 0; t < D; ++t) {
-                    r[t] = X[(size_t)i * D + t];
+                    r[t] = Xg[(size_t)i * D + t];
                     fq = max(fq, frac_bits(r[t]));
                     amax = fmaxf(amax, fabsf(r[t]));
                 }
@@ -186,10 +189,10 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
                 float h = 0.f;
 #pragma unroll
                 for (int t = 0; t < D; ++t) {
-                    float xc = X[(size_t)i * D + t] - centre[t];
-                    r[t] = X[(size_t)i * D + t];
+                    float xc = Xg[(size_t)i * D + t] - centre[t];
+                    r[t] = Xg[(size_t)i * D + t];
                     h = fmaf(xc, xc, h);
-                    fq = max(fq, centred_bits(X[(size_t)i * D + t], centre[t], xc));
+                    fq = max(fq, centred_bits(Xg[(size_t)i * D + t], centre[t], xc));
                     amax = fmaxf(amax, fabsf(xc));
                 }
                 r[D] = h;

@@ -39,18 +39,19 @@ namespace rc {
 constexpr int kWave = 64;
 
 // LDS arrays of one pair; I is the index type (int32_t, or uint16_t in the
-// compact layout of the point path, where sorted and list share storage).
+// compact layout).  In the bucket-major phases ckey, cnn and list go by bucket
+// position once the buckets are formed.
 template <typename I>
 struct LdsT {
     double* smass;  // [M] supplier mass (by local index while loading, then by active slot)
     double* cmass;  // [N] consumer mass by local index
-    double* ckey;   // [N] FP64 key of (pick, j); after the serve: flow (0 = unserved)
+    double* ckey;   // [N] FP64 key of (pick, j); consumer-major after the serve: flow (0 = unserved)
     float* srec;    // [M * RS] active supplier records, compacted
     I* sidx;        // [M] local index of active supplier slot
     I* scnt;        // [M] claimant count by active slot
     I* soff;        // [M] bucket start, then bucket end, by active slot
     I* cact;        // [N] active consumers, compacted, ascending
-    I* cnn;         // [N] pick (active slot) by consumer; after the serve: supplier local index
+    I* cnn;         // [N] pick (active slot) by consumer; consumer-major after the serve: supplier local index
     I* list;        // [N] near-tie consumers during the search; claimant buckets after
     I* sorted;      // [N] claimant buckets in serve order (the list's storage when shared)
     float* yl;      // [N * cd] consumer coordinates by local index (coordinate variant only)

@@ -13,10 +13,10 @@
 // activations, pooling and the optimiser are FP32.
 //
 // Kernels: a generic BF16 "NT" GEMM on v_mfma_f32_16x16x32_bf16 (C = A B^T,
-// both operands K-contiguous), a fused phi + pooling
-// kernel for inference (one workgroup per set, no workspace), unfused layer
-// kernels for training, LDS transposes, deterministic column sums, Adam, and
-// a radix top-k.
+// both operands K-contiguous), a fused phi + pooling kernel (persistent
+// workgroups, no workspace; the training forward runs it with the points of a
+// set added in order), the fused backward of pooling and both point layers, LDS
+// transposes, deterministic column sums, Adam, and a radix top-k.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -241,7 +241,8 @@ __device__ inline void layer1_tile(const float4* xs, int np, const float (&w)[2]
 // Fused inference: persistent workgroups, each walking the 64-point chunks of
 // its sets: layer 1 into LDS (BF16), layer 2 on the matrix cores (each
 // wavefront 64 points x 64 outputs, its 32 KB of W2 held in 128 registers for
-// the whole launch; 14 to 16 other values of a lane are spilled), bias + ReLU + mass weighting, column sums in registers.
+// the whole launch; 14 to 16 other values of a lane are spilled), bias + ReLU +
+// mass weighting, column sums in registers.
 // The next chunk's points are loaded while the current one multiplies.
 // Bound: a chunk is 2.0 k cycles of matrix pipe per SIMD; the vector work
 // (layer 1 about 350 instructions a thread with the packed BF16 conversion,
