@@ -298,11 +298,14 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 // (four waves per SIMD, so small pairs keep four workgroups per CU), 168 for
 // d = 4, 5 and 256 for d = 6, 7, whose larger LDS records hold a 1024-point pair
 // to two or three workgroups per CU anyway; no variant spills with these.  Two
-// points per thread of 512 (1024 pairs of 128..1024 points, d = 3): held to 80
-// VGPRs, 27 to 32 registers of the matrix-core search spill, 557 us, with 128
-// 503; the L1 search spills 4 to 10 with 80, 506 us, none with 96, 522.
+// points per thread of 512, d <= 3, are held to 80 (six waves, three workgroups
+// per CU) although 27 to 32 registers of the matrix-core search spill (L1 4 to
+// 10): with 128 VGPRs 4096 pairs of 128..1024 points, d = 3, take 1260 us
+// instead of 1189 and of 62..500 points 845 instead of 773.  (Launches that do
+// not fill the chip would gain: 1024 of those pairs 553 -> 503 us, one 512-point
+// pair 134 -> 118.)
 template <int D, int T, int CSMAX, bool L1, bool CL>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 && L1 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
 void pair_solver_kernel(PairSolverArgs A) {
     extern __shared__ __align__(16) char lds_dyn[];
     __shared__ SharedCore sh;
