@@ -8,9 +8,11 @@ before timing; the timed region is exactly --steps launches bracketed by
 device synchronisation, measured with events on the launch stream.
 
 Also reported on the same inputs:
-  * roofline of the solver kernel (VALU-bound: algorithmic work is
-    sum over rounds of |active S| x |active C| pair evaluations, 2d+2 lane
-    operations each, against 256 CUs x 64 lanes x 2.4 GHz);
+  * roofline of the solver kernel (algorithmic work is the sum over rounds
+    of |active S| x |active C| pair evaluations, 2d+2 operations each: the
+    fused multiply-adds of the key, which run on the FP32 matrix
+    instruction, against its 157.3 TFLOP/s), and the share of the vector
+    issue slots that the selection of the best two keys takes;
   * the plain single-pair FP32 path (one emd_approx launch per pair);
   * the oracle (FP64, CPU, OpenMP over pairs) on the same pairs, which is
     also the parity check of the timed outputs.
@@ -33,6 +35,9 @@ sys.path.insert(0, ROOT)
 # lane-operations per second (half the 157.3 TFLOP/s FP32 figure, which counts
 # a packed FMA as four flops; packed FP32 is not used by these kernels).
 PEAK_VALU_LANE_OPS = 256 * 64 * 2.4e9
+# FP32 matrix instruction (16 x 16 x 4: 2048 flops in 32 cycles of a SIMD),
+# which the point search's keys and the k-means scan run on.
+PEAK_FP32_MFMA = 256 * 4 * 64 * 2.4e9
 # Dense BF16 matrix-core peak of MI355X (2.5 PFLOP/s, no sparsity) and HBM3E.
 PEAK_BF16_MFMA = 2.5e15
 PEAK_HBM = 8.0e12
@@ -87,10 +92,10 @@ def measured_doc_traffic():
     return t.get("bytes_per_call")
 
 
-def issued_per_eval(d):
-    """VALU instructions the point-path search loop issues per evaluation
-    (counted in the gfx950 assembly of the unrolled block)."""
-    return d + 1.6875
+# VALU instructions that the matrix-core search issues per evaluation, d <= 3
+# (counted in the gfx950 assembly of the unrolled loop: 129 per 16 blocks of
+# 16 records x 16 consumers beside 16 matrix instructions, 64 lanes each).
+ISSUED_PER_EVAL = 129 * 64 / (16 * 256)
 
 
 def measured_traffic(per_launch_algorithmic_bytes):
@@ -259,21 +264,18 @@ def main():
     alg_bytes = int(ps.X.nbytes + ps.a.nbytes + ps.Y.nbytes + ps.b.nbytes + ps.x_off.nbytes
                     + ps.y_off.nbytes + P * (8 + binding.STATS_BYTES) + (int(st["nnz"].sum()) * 16 if want_plan else 0))
     threads_used = args.threads or (tuning["threads"] if tuning else 256)
-    roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_VALU_LANE_OPS / 1e12,
-                "unit": "Tops/s", "frac": achieved / PEAK_VALU_LANE_OPS,
+    roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
+                "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA,
                 "traffic": measured_traffic(alg_bytes),
                 "kernel": "pair_solver_kernel<3,%d,%d,L2> + order_kernel (one step)" % (
                     threads_used, -(-max(max_m, max_n) // threads_used)),
                 "work_evals": work,
                 "ops_per_eval": 2 * d + 2, "algorithmic_bytes": alg_bytes,
                 "hbm_gbs_algorithmic": alg_bytes / (ms / 1e3) / 1e9,
-                # the search loop issues d + 1.6875 VALU instructions per
-                # evaluation (per block of 8 records x 4 consumers: 32 d FMAs,
-                # 16 med3 and 24 min3 for the best two keys, 14 for the
-                # block's slot bookkeeping): the share of the VALU issue
-                # slots that went to evaluations
-                "issued_ops_per_eval": issued_per_eval(d),
-                "issue_frac": work * issued_per_eval(d) / (ms / 1e3) / PEAK_VALU_LANE_OPS}
+                # the share of the VALU issue slots that went to the selection
+                # of the best two keys
+                "issued_ops_per_eval": ISSUED_PER_EVAL,
+                "issue_frac": work * ISSUED_PER_EVAL / (ms / 1e3) / PEAK_VALU_LANE_OPS}
 
     single = None
     if not args.no_single_pair:
@@ -418,8 +420,8 @@ def bench_lattice_sweep(args, dev):
     N = ps.num_pairs
     ms = row["greedy"]["batched_ms"]
     work = row["greedy"]["work_evals"]
-    roofline = {"bound": "alu", "achieved": work * 6 / (ms / 1e3) / 1e12, "peak": PEAK_VALU_LANE_OPS / 1e12,
-                "unit": "Tops/s", "frac": work * 6 / (ms / 1e3) / PEAK_VALU_LANE_OPS, "traffic": None,
+    roofline = {"bound": "alu", "achieved": work * 6 / (ms / 1e3) / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
+                "unit": "TFLOP/s", "frac": work * 6 / (ms / 1e3) / PEAK_FP32_MFMA, "traffic": None,
                 "kernel": "pair_solver_kernel<2,...> (exact-key lattice search) at N = 16384",
                 "work_evals": work, "ops_per_eval": 6}
     cpu = None
@@ -473,12 +475,13 @@ def bench_colour_app(args, dev):
     ms = e0.elapsed_time(e1) / steps
     st = binding.stats_numpy(r["stats"])[0]
     # dominant work: the palette reduction, 2 images x 11 assignment passes x
-    # 1M pixels x 256 centroids, each distance 3 FP64 subtracts, 3 multiplies,
-    # 3 adds (no fused multiply-add)
-    flops = 2 * 11 * (1024 * 1024) * 256 * 9.0
-    roofline = {"bound": "alu", "achieved": flops / (ms / 1e3) / 1e12, "peak": 78.6 / 2,
-                "unit": "FP64 TFLOP/s (non-fused)", "frac": flops / (ms / 1e3) / 39.3e12, "traffic": None,
-                "kernel": "km_assign (k-means assignment, FP64, one thread per pixel)", "flops_per_step": flops}
+    # 1M pixels x 256 centroids, each key four fused multiply-adds of the FP32
+    # matrix instruction
+    flops = 2 * 11 * (1024 * 1024) * 256 * 8.0
+    roofline = {"bound": "alu", "achieved": flops / (ms / 1e3) / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
+                "unit": "TFLOP/s", "frac": flops / (ms / 1e3) / PEAK_FP32_MFMA, "traffic": None,
+                "kernel": "km_assign (k-means assignment: FP32 matrix-core scan, FP64 where the best two are close)",
+                "flops_per_step": flops}
     cpu = parity = None
     if not args.no_cpu_baseline:
         import oracle
@@ -534,8 +537,8 @@ def bench_single_pair(args, dev):
     assert int(st["status"]) == 0
     work = int(st["work"])
     achieved = work * (2 * ps.d + 2) / (ms / 1e3)
-    roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_VALU_LANE_OPS / 1e12, "unit": "Tops/s",
-                "frac": achieved / PEAK_VALU_LANE_OPS, "traffic": None,
+    roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32_MFMA / 1e12, "unit": "TFLOP/s",
+                "frac": achieved / PEAK_FP32_MFMA, "traffic": None,
                 "kernel": "pair_solver_kernel (one workgroup): latency-bound, "
                           "rounds x barrier-separated phases; the whole-GPU fraction does not describe it",
                 "work_evals": work, "ops_per_eval": 2 * ps.d + 2}
@@ -628,8 +631,8 @@ def bench_colour_transfer(args, dev):
 def bench_documents(args, dev):
     """One 300-d BF16 query against 8192 ragged candidates (20..500 points,
     Zipf(1.1) masses, L2) through the high-dimensional path: key tiles on the
-    matrix cores.  Compared on the same values with the batched FP32 vector
-    path and the plain single-pair FP32 path (one emd_approx per pair)."""
+    matrix cores.  Compared on the same values with the batched FP32
+    path (FP32 matrix instruction) and the plain single-pair FP32 path (one emd_approx per pair)."""
     import numpy as np
     import torch
 
@@ -694,11 +697,11 @@ def bench_documents(args, dev):
     out_v = buffers()
     vsteps = max(1, min(args.steps, 5))
     ms_v = timed(Xf, Yf, "fp32", out_v, vsteps)
-    # The FP32 vector path recomputes every served distance in FP64; the BF16
+    # The FP32 path recomputes every served distance in FP64; the BF16
     # split form takes them from its keys within 1e-5 (plans identical).
     vcosts = out_v["costs"].cpu().numpy()[:P]
     v_rel = float(np.max(np.abs(vcosts - costs) / np.maximum(np.abs(vcosts), 1e-300)))
-    log(f"batched FP32 vector path {ms_v:.3f} ms/step; max rel cost difference {v_rel:.3g}")
+    log(f"batched FP32 path {ms_v:.3f} ms/step; max rel cost difference {v_rel:.3g}")
 
     single = None
     if not args.no_single_pair:
