@@ -47,8 +47,8 @@ __host__ __device__ inline int km_pad(int K) { return (K + 15) & ~15; }
 // K = 16 5570 us so, 752 with this; K = 256 7730 and 1209; FP64 distances to
 // every centroid, before the scan, took 1075 and 2425).  look: whether there may
 // be equal ones; they meet in a hash table (at most half full, linear probing,
-// so every probe ends).  Not called when the centroids themselves are compared
-// (km_assign_direct; rec null).
+// so every probe ends).  Not made (RECORDS false) where the centroids themselves
+// are compared (km_assign_direct).
 __device__ void km_records(int K, bool look, double c0, double c1, double c2, float4* __restrict__ rec) {
 #pragma clang fp contract(off)
     __shared__ double cc[3 * kKmMax];
@@ -95,6 +95,7 @@ __device__ void km_records(int K, bool look, double c0, double c1, double c2, fl
     }
 }
 
+template <bool RECORDS>
 __global__ __launch_bounds__(kKmMax) void km_init(const uint8_t* __restrict__ px, int64_t P, int K,
                                                   double* __restrict__ C, unsigned long long* __restrict__ S,
                                                   float4* __restrict__ rec) {
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(kKmMax) void km_init(const uint8_t* __restrict__ px
 #pragma unroll
         for (int t = 0; t < 4; ++t) S[k * 4 + t] = 0ull;
     }
-    if (rec != nullptr) km_records(K, true, c[0], c[1], c[2], rec);
+    if constexpr (RECORDS) km_records(K, true, c[0], c[1], c[2], rec);
 }
 
 // One assignment step: every pixel to its nearest centroid; the cluster
@@ -317,6 +318,7 @@ __global__ __launch_bounds__(kKmThreads) void km_assign_direct(const uint8_t* __
 }
 
 // Update from the sums of the last assignment, then clear them for the next.
+template <bool RECORDS>
 __global__ __launch_bounds__(kKmMax) void km_update(int K, double* __restrict__ C,
                                                     unsigned long long* __restrict__ S, float4* __restrict__ rec) {
     const int k = threadIdx.x;
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(kKmMax) void km_update(int K, double* __restrict__ 
     }
     // the later of two equal centroids is empty (two clusters whose means have
     // just become equal are found one pass later)
-    if (rec != nullptr) km_records(K, __syncthreads_or(empty) != 0, c[0], c[1], c[2], rec);
+    if constexpr (RECORDS) km_records(K, __syncthreads_or(empty) != 0, c[0], c[1], c[2], rec);
 }
 
 // Palette histogram from the final assignment's counts.
@@ -386,7 +388,7 @@ int launch_kmeans(const uint8_t* px, int64_t P, int K, int iters, double* C, uns
     // and 390 us, 512 x 512 604 and 548, 720 x 720 the same)
     const int64_t pieces = (P + kKmThreads - 1) / kKmThreads;
     const bool direct = K <= kKmDirectMax && pieces < 512;
-    float4* rec = direct ? nullptr : reinterpret_cast<float4*>(records);
+    float4* rec = reinterpret_cast<float4*>(records);
     const int groups = (int)std::max<int64_t>(1, std::min<int64_t>(kKmGroups, pieces / 512));
     const unsigned pb = (unsigned)((pieces + groups - 1) / groups);
     const size_t lds = kmeans_lds_bytes(K);
@@ -395,13 +397,18 @@ int launch_kmeans(const uint8_t* px, int64_t P, int K, int iters, double* C, uns
                                                  (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(km_init, dim3(1), dim3(kt), 0, st, px, P, K, C, S, rec);
-    for (int it = 0; it <= iters; ++it) {
-        if (direct)
+    if (direct) {
+        hipLaunchKernelGGL(km_init<false>, dim3(1), dim3(kt), 0, st, px, P, K, C, S, rec);
+        for (int it = 0; it <= iters; ++it) {
             hipLaunchKernelGGL(km_assign_direct, dim3((unsigned)pieces), dim3(kKmThreads), 0, st, px, P, K, C, S, assign);
-        else
+            if (it < iters) hipLaunchKernelGGL(km_update<false>, dim3(1), dim3(kt), 0, st, K, C, S, rec);
+        }
+    } else {
+        hipLaunchKernelGGL(km_init<true>, dim3(1), dim3(kt), 0, st, px, P, K, C, S, rec);
+        for (int it = 0; it <= iters; ++it) {
             hipLaunchKernelGGL(km_assign, dim3(pb), dim3(kKmThreads), lds, st, px, P, K, groups, C, rec, S, assign);
-        if (it < iters) hipLaunchKernelGGL(km_update, dim3(1), dim3(kt), 0, st, K, C, S, rec);
+            if (it < iters) hipLaunchKernelGGL(km_update<true>, dim3(1), dim3(kt), 0, st, K, C, S, rec);
+        }
     }
     hipLaunchKernelGGL(km_palette, dim3(kb), dim3(kKmThreads), 0, st, K, P, C, S, pts, mass);
     return (int)hipGetLastError();
