@@ -9,7 +9,7 @@
 //      active supplier records in FP32 (point_search.hpp).  For the Euclidean
 //      metrics the record holds x and ||x^||^2 with x^ = x - centre, and the
 //      key ||x^||^2 - 2 x^.y^ equals ||x^ - y^||^2 - ||y^||^2 up to a rounding
-//      bound E_q; 64 consumers and more are compared on the FP32 matrix
+//      bound E_q; 32 consumers and more are compared on the FP32 matrix
 //      instruction, fewer (and L1) on the vector ALUs.  Best and second-best
 //      keys are tracked and a consumer whose two keys are within that bound is
 //      re-scored in FP64 by a whole wavefront, so every pick equals the FP64

@@ -495,9 +495,13 @@ __device__ inline void nns_tiles(const LT& L, SharedCore& sh, const float* __res
 // active consumer gets its S lanes.
 // Consumers from which the search runs on the matrix cores.  Fewer: several
 // lanes of the vector form share a consumer, which fills the workgroup where
-// 16-consumer tiles would leave wavefronts idle.  (64, 128 and 256 timed
-// within 2 % of each other on 256- to 1024-point pairs.)
-constexpr int kTileConsumers = 64;
+// 16-consumer tiles would leave wavefronts idle.  Two tiles on two wavefronts
+// are level with the vector form at d <= 3 and ahead of it at d >= 4, whose
+// centring costs d subtractions a key: 64 against 32 as the line, 64 pairs of
+// 64..512 points, d = 7, 273 and 265 us, one pair of 1000 x 64 points, d = 6, 265
+// and 235, 1024 pairs of 128..1024, d = 3, 525 and 521.  At 16, one tile, small
+// pairs lose (200 x 30 points, d = 3, 76.7 and 78.4).
+constexpr int kTileConsumers = 32;
 template <int D, int T, int CSMAX, bool L1, typename LT>
 __device__ inline int search_round(const LT& L, SharedCore& sh, const float* __restrict__ Y,
                                    const float (&centre)[D], float rhat, int mact, int nact, int split, bool exact, int metric) {

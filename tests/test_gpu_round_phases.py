@@ -89,10 +89,10 @@ def test_centre_below_the_coordinates_last_fp64_bit(d, y, protocol):
 @pytest.mark.parametrize("kind", ["unit", "mixed", "tiny", "large"])
 @pytest.mark.parametrize("d", [1, 3, 4, 7])
 def test_matrix_core_keys_are_the_vector_keys(d, kind):
-    """The matrix-core search (64 consumers and more) finds its slot by the
+    """The matrix-core search (32 consumers and more) finds its slot by the
     equality of its keys with the fused multiply-add chain's; a key without an
     equal is re-scored.  One round of 128 consumers must therefore re-score as
-    many as the vector search of the same consumers in four calls of 32, also
+    many as the vector search of the same consumers in eight calls of 16, also
     where products and norms are subnormal or span many binades."""
     rng = np.random.default_rng(40 + d)
     m, n = 301, 128
@@ -106,11 +106,23 @@ def test_matrix_core_keys_are_the_vector_keys(d, kind):
     X, Y = points(m), points(n)
     a, b = np.full(m, 1.0 / m, np.float32), np.full(n, 1.0 / n, np.float32)
     whole = int(gpu_pair(X, a, Y, b, max_rounds=1)["stats"]["rescored"])
-    b4 = np.full(32, 1.0 / 32, np.float32)
-    parts = [int(gpu_pair(X, a, Y[k:k + 32], b4, max_rounds=1)["stats"]["rescored"]) for k in range(0, n, 32)]
+    b8 = np.full(16, 1.0 / 16, np.float32)
+    parts = [int(gpu_pair(X, a, Y[k:k + 16], b8, max_rounds=1)["stats"]["rescored"]) for k in range(0, n, 16)]
     assert whole == sum(parts)
     assert whole < n or kind in ("tiny", "mixed")
     assert_pair_matches(gpu_pair(X, a, Y, b), oracle_pair(X, a, Y, b), label=kind)
+
+
+@pytest.mark.parametrize("mn", [(300, 31), (300, 32), (15, 33), (1000, 48), (17, 49)], ids=lambda v: "%dx%d" % v)
+@pytest.mark.parametrize("d", [1, 3, 4, 7])
+def test_few_consumers(mn, d):
+    """Consumer counts around the line between the vector search and two or
+    three matrix-core tiles, with and without ties."""
+    m, n = mn
+    for lattice in (0, 6):
+        X, a, Y, b = W.random_pair(m + 7 * n + d, m, n, d, masses="integer" if lattice else "dirichlet", lattice=lattice)
+        for threads in (256, 512):
+            assert_pair_matches(gpu_pair(X, a, Y, b, threads=threads), oracle_pair(X, a, Y, b), label=f"{mn}-{lattice}")
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
