@@ -299,11 +299,11 @@ __device__ void solve_pair(const PairSolverArgs& A, int64_t p, const Lds16& L, S
 // d = 4, 5 and 256 for d = 6, 7, whose larger LDS records hold a 1024-point pair
 // to two or three workgroups per CU anyway; no variant spills with these.  Two
 // points per thread of 512, d <= 3, are held to 80 (six waves, three workgroups
-// per CU) although 27 to 32 registers of the matrix-core search spill (L1 4 to
+// per CU) although 20 to 26 registers of the matrix-core search spill (L1 4 to
 // 10): with 128 VGPRs 4096 pairs of 128..1024 points, d = 3, take 1260 us
-// instead of 1189 and of 62..500 points 845 instead of 773.  (Launches that do
-// not fill the chip would gain: 1024 of those pairs 553 -> 503 us, one 512-point
-// pair 134 -> 118.)
+// instead of 1160 and of 62..500 points 845 instead of 711.  (Launches that do
+// not fill the chip would gain: 1024 of those pairs 545 -> 503 us, one 512-point
+// pair 129 -> 118.)
 template <int D, int T, int CSMAX, bool L1, bool CL>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(CSMAX == 2 && D <= 3 ? 6 : (CSMAX <= 4 ? (D <= 3 ? 4 : (D <= 5 ? 3 : 2)) : 1))))
 void pair_solver_kernel(PairSolverArgs A) {

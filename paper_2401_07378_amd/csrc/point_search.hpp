@@ -518,12 +518,16 @@ __device__ inline int search_round(const LT& L, SharedCore& sh, const float* __r
     if (!L1 && (S == 1 || nact >= kTileConsumers)) {
         const int nt = (nact + 15) / 16;
         const int lo = wave * nt / NW, hi = (wave + 1) * nt / NW;
-        for (int t0 = lo; t0 < hi; t0 += 4) {
+        // most tiles of a pass: the 512-thread variants held to 80 VGPRs take two,
+        // which spill 20 to 26 registers where four spill 27 to 32 (4096 pairs of
+        // 128..1024 points, d = 3, 1215 -> 1160 us, of 62..500 points 801 -> 711)
+        constexpr int KT = T == 512 && CSMAX == 2 && D <= 3 ? 2 : 4;
+        for (int t0 = lo; t0 < hi; t0 += KT) {
             const int k = hi - t0;  // wavefront-uniform
-            const int qend = min(nact, 16 * hi);  // three tiles run as four, the last one idle
-            if (k >= 3)
-                nns_tiles<D, RS, 4>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
-            else if (k == 2)
+            const int qend = min(nact, 16 * hi);  // three tiles of a pass of four run as four, the last one idle
+            if (KT == 4 && k >= 3)
+                nns_tiles<D, RS, KT>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
+            else if (k >= 2)
                 nns_tiles<D, RS, 2>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
             else
                 nns_tiles<D, RS, 1>(L, sh, Y, centre, rhat, mact, qend, 16 * t0, exact, metric);
